@@ -372,10 +372,11 @@ GLCM_API int glcm_haralick(const uint32_t *glcm, int K, int N, float *out, void 
  * in the introduction with the others): out[k] = the square root of the
  * second largest eigenvalue of Q(i, j) = sum_c p(i, c) p(j, c) / (px(i) py(c)),
  * p = P[k] / T, px and py the row and column marginals; terms with a zero
- * marginal are 0.  Computed in fp64 from the symmetric matrix S = B B^T,
- * B(i, c) = p(i, c) / sqrt(px(i) py(c)), which has Q's eigenvalues, with cyclic
- * Jacobi rotations (at most 30 sweeps); stored as fp32.  T = 0 or N = 1 gives
- * 0.  glcm as above; N <= 64 (GLCM_EUNSUPPORTED above); out: K float, device
+ * marginal are 0.  Computed in fp64 from B(i, c) = p(i, c) / sqrt(px(i) py(c)),
+ * whose singular values are the square roots of Q's eigenvalues: the largest
+ * (1, with vectors sqrt(px), sqrt(py)) is subtracted and the next one is found
+ * by squaring the symmetric matrix that remains; stored as fp32.  T = 0 or
+ * N = 1 gives 0.  glcm as above; N <= 64 (GLCM_EUNSUPPORTED above); out: K float, device
  * memory.  Errors as for glcm_haralick.
  */
 GLCM_API int glcm_haralick_mcc(const uint32_t *glcm, int K, int N, float *out, void *stream);

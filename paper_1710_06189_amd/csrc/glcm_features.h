@@ -6,6 +6,8 @@
 
 #include <cstdint>
 
+#include "glcm_wave.h"
+
 namespace glcm {
 namespace {
 
@@ -19,40 +21,6 @@ namespace {
 // words, redf: 3 blockDim / 64 words of workgroup scratch.  Every thread of
 // the workgroup must call it.
 // ---------------------------------------------------------------------------
-// Wavefront sum by DPP lane moves (no LDS round trips): prefix sums within
-// each row of 16 lanes (row_shr 1, 2, 4, 8), then lane 15 of rows 0 and 2 is
-// added into rows 1 and 3 (row_bcast:15) and lane 31 into rows 2 and 3
-// (row_bcast:31), leaving the total in lane 63, which is returned to all.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ uint32_t dpp_move(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, true);
-}
-template <int CTRL, int ROWS>
-__device__ __forceinline__ unsigned long long dpp_move(unsigned long long v) {
-  return (unsigned long long)dpp_move<CTRL, ROWS>((uint32_t)v) |
-         ((unsigned long long)dpp_move<CTRL, ROWS>((uint32_t)(v >> 32)) << 32);
-}
-template <int CTRL, int ROWS>
-__device__ __forceinline__ float dpp_move(float v) {
-  return __uint_as_float(dpp_move<CTRL, ROWS>(__float_as_uint(v)));
-}
-__device__ __forceinline__ uint32_t lane63(uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)v, 63); }
-__device__ __forceinline__ unsigned long long lane63(unsigned long long v) {
-  return (unsigned long long)lane63((uint32_t)v) | ((unsigned long long)lane63((uint32_t)(v >> 32)) << 32);
-}
-__device__ __forceinline__ float lane63(float v) { return __uint_as_float(lane63(__float_as_uint(v))); }
-
-template <typename T>
-__device__ __forceinline__ T wave_sum(T v) {
-  v += dpp_move<0x111, 0xf>(v);  // row_shr:1
-  v += dpp_move<0x112, 0xf>(v);  // row_shr:2
-  v += dpp_move<0x114, 0xf>(v);  // row_shr:4
-  v += dpp_move<0x118, 0xf>(v);  // row_shr:8
-  v += dpp_move<0x142, 0xa>(v);  // row_bcast:15 into rows 1, 3
-  v += dpp_move<0x143, 0xc>(v);  // row_bcast:31 into rows 2, 3
-  return lane63(v);
-}
-
 // The five statistics from the exact integer sums and the fp32 sums.
 __device__ __forceinline__ void features_store(unsigned long long T, unsigned long long sc, unsigned long long si,
                                                unsigned long long sj, unsigned long long sii, unsigned long long sjj,

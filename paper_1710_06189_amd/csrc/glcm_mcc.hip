@@ -1,160 +1,191 @@
 // Haralick's maximal correlation coefficient (the fourteenth statistic) of K
-// co-occurrence matrices, fp64 on the device.
+// co-occurrence matrices, fp64 on the matrix cores.
 
 #include <hip/hip_runtime.h>
 
 #include "glcm_device.h"
 #include "glcm_stats.h"
+#include "glcm_wave.h"
 
 namespace glcm {
 namespace {
 
-// Wavefront sums by butterfly: every lane ends with the same bits (each step
-// adds the same two values on both lanes of a pair), so decisions taken on
-// them are uniform.
-__device__ __forceinline__ double wave_sum_f64(double v) {
-  for (int o = 32; o; o >>= 1) v += __shfl_xor(v, o);
-  return v;
-}
+typedef double d4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
-  for (int o = 32; o; o >>= 1) v += (uint64_t)__shfl_xor((unsigned long long)v, o);
-  return v;
-}
-
-unsigned grid_for(int units) { return (unsigned)(units < 8192 ? (units > 0 ? units : 1) : 8192); }
+constexpr int kMccThreads = 256;
+constexpr int kMccWaves = kMccThreads / 64;
+// Squarings at most: a spectrum whose largest eigenvalue repeats never becomes
+// rank one, and then the estimate's relative error is below ln(N) / 2^34.
+constexpr int kMccSquarings = 34;
+constexpr double kMccTol = 1e-5;
 
 // Haralick's fourteenth statistic, the maximal correlation coefficient: the
 // square root of the second largest eigenvalue of
-// Q(i, j) = sum_c p(i, c) p(j, c) / (px(i) py(c)).  Q is similar to the
-// symmetric S = B B^T with B(i, c) = p(i, c) / sqrt(px(i) py(c)) (0 where a
-// marginal is 0), so the kernel forms S in LDS and diagonalises it with cyclic
-// Jacobi rotations in fp64 (at most kMccSweeps sweeps, stopping once the
-// off-diagonal norm is below 1e-13 of the diagonal's).  One 64-lane
-// workgroup per matrix, N <= kMccMaxLevels.
-constexpr int kMccSweeps = 30;
-
-__global__ __launch_bounds__(64) void k_haralick_mcc(StatsArgs a) {
-  extern __shared__ double mcc_sh[];  // B[N][N], S[N][N], rx[N], ry[N]
-  const int N = a.N, lane = threadIdx.x;
-  const uint32_t NN = (uint32_t)N * (uint32_t)N;
-  double* Bm = mcc_sh;
-  double* Sm = Bm + NN;
-  double* rx = Sm + NN;
-  double* ry = rx + N;
-  __shared__ int rp[kMccMaxLevels / 2], rq[kMccMaxLevels / 2];  // the pairs of a round
-  __shared__ double rc[kMccMaxLevels / 2], rs[kMccMaxLevels / 2];  // and their rotations
-  for (int k = blockIdx.x; k < a.K; k += gridDim.x) {
-    const uint32_t* P = a.in + (size_t)k * NN;
-    uint64_t t = 0;
-    for (uint32_t r = lane; r < NN; r += 64) t += P[r];
-    const uint64_t T = wave_sum_u64(t);
-    if (T == 0 || N == 1) {
+// Q(i, j) = sum_c p(i, c) p(j, c) / (px(i) py(c)).  Q is similar to B B^T with
+// B(i, c) = p(i, c) / sqrt(px(i) py(c)), whose largest singular triple is
+// known: 1, sqrt(px), sqrt(py).  The kernel subtracts it,
+//     D(i, c) = (p(i, c) - px(i) py(c)) / sqrt(px(i) py(c)),
+// the numerator as c T - row(i) col(c) in exact integers held in doubles (one
+// rounding each, no cancellation), and needs the largest eigenvalue of
+// S = D D^T.  Squaring M_0 = S / tr S again and again,
+//     f_j = tr(M_j^2) = |M_j|_F^2,   M_{j+1} = M_j^2 / f_j,
+// gives it as tr S * prod_j f_j^(1 / 2^(j+1)); a rounding error of squaring j
+// enters divided by 2^j.  With M_j's other eigenvalues summing to
+// s <= (1 - f_j) the product's next factors are 1 within s^2 / 2^j, so it ends
+// once 1 - f_j < 1e-5.  (M_j^2 is scaled by an approximate 1 / f_j, s_j, whose
+// exact value goes into the product.)
+//
+// One wavefront per matrix (TB x TB tiles of 16 x 16, zero padded): lane l =
+// 16 g + i holds D(16 a + i, 16 c + 4 g + v), v < 4, of every tile (a, c),
+// which is both operands of S's v_mfma_f64_16x16x4; and since S is symmetric
+// a result tile, lane l holding rows r(g, v) of column i, is both operands of
+// the next squaring whatever r is, so no value ever moves between lanes.
+//
+// Bound: the fp64 matrix rate (a squaring at N = 16 is four instructions of 64
+// cycles, seven or so squarings a matrix) and the wavefront sum between two
+// squarings.  Measured on MI355X, 16384 matrices of N = 16: 36 us a call (57 us
+// with one logarithm per squaring and a tolerance of 1e-10); cyclic Jacobi
+// rotations of S in LDS, the form before this one, took 2750 us (three
+// barriers for each of fifteen rounds of five or so sweeps).
+template <int TB>
+__global__ __launch_bounds__(kMccThreads, TB <= 2 ? 2 : 1) void k_haralick_mcc(StatsArgs a) {
+  const int N = a.N, lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
+  const int nwaves = (int)gridDim.x * kMccWaves;
+  for (int k = (int)blockIdx.x * kMccWaves + (int)(threadIdx.x >> 6); k < a.K; k += nwaves) {
+    const uint32_t* P = a.in + (size_t)k * (size_t)N * (size_t)N;
+    d4 D[TB][TB];
+    double rs[TB], cs[TB][4];  // row sums (of row 16 a + i) and column sums (of column 16 c + 4 g + v)
+#pragma unroll
+    for (int c = 0; c < TB; ++c)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) cs[c][v] = 0.0;
+#pragma unroll
+    for (int r = 0; r < TB; ++r) {
+      double s = 0.0;
+#pragma unroll
+      for (int c = 0; c < TB; ++c)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int y = 16 * r + i, x = 16 * c + 4 * g + v;
+          const double p = (y < N && x < N) ? (double)P[y * N + x] : 0.0;
+          D[r][c][v] = p;
+          s += p;
+          cs[c][v] += p;
+        }
+      rs[r] = sum_xor32(sum_xor16(s));
+    }
+    double T = 0.0;
+#pragma unroll
+    for (int r = 0; r < TB; ++r) T += rs[r];
+    T = row16_sum(T);
+    if (T == 0.0) {  // (uniform; N = 1 has D = 0 below)
       if (lane == 0) a.out_f[k] = 0.0f;
       continue;
     }
-    const double inv = 1.0 / (double)T;
-    if (lane < N) {
-      uint64_t sx = 0, sy = 0;
-      for (int c = 0; c < N; ++c) sx += P[lane * N + c];
-      for (int i = 0; i < N; ++i) sy += P[i * N + lane];
-      rx[lane] = sx ? 1.0 / sqrt((double)sx * inv) : 0.0;
-      ry[lane] = sy ? 1.0 / sqrt((double)sy * inv) : 0.0;
+    const double invT = 1.0 / T;
+    double wr[TB], wc[TB][4];  // 1 / sqrt of the marginals, 0 where a marginal is 0
+#pragma unroll
+    for (int r = 0; r < TB; ++r) wr[r] = rs[r] > 0.0 ? rsqrt(rs[r]) * invT : 0.0;
+#pragma unroll
+    for (int c = 0; c < TB; ++c) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) cs[c][v] = row16_sum(cs[c][v]);
+      // lane q of a quad takes column 4 g + q's square root for its group
+      const int q = i & 3;
+      const double c0 = cs[c][0], c1 = cs[c][1], c2 = cs[c][2], c3 = cs[c][3];
+      const double own = q == 0 ? c0 : (q == 1 ? c1 : (q == 2 ? c2 : c3));
+      const double w = own > 0.0 ? rsqrt(own) : 0.0;
+      wc[c][0] = quad_bcast<0>(w);
+      wc[c][1] = quad_bcast<1>(w);
+      wc[c][2] = quad_bcast<2>(w);
+      wc[c][3] = quad_bcast<3>(w);
     }
-    __syncthreads();
-    for (uint32_t r = lane; r < NN; r += 64) {
-      const uint32_t i = divide(r, a.nmagic, a.nshift), c = r - i * (uint32_t)N;
-      Bm[r] = (double)P[r] * inv * rx[i] * ry[c];
+    double t0 = 0.0;
+#pragma unroll
+    for (int r = 0; r < TB; ++r)
+#pragma unroll
+      for (int c = 0; c < TB; ++c)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const double prod = rs[r] * cs[c][v], perr = fma(rs[r], cs[c][v], -prod);
+          const double d = (fma(D[r][c][v], T, -prod) - perr) * wr[r] * wc[c][v];
+          D[r][c][v] = d;
+          t0 += d * d;
+        }
+    t0 = wave_sum(t0);  // tr S
+    if (!(t0 > 0.0)) {
+      if (lane == 0) a.out_f[k] = 0.0f;
+      continue;
     }
-    __syncthreads();
-    for (uint32_t r = lane; r < NN; r += 64) {
-      const uint32_t i = divide(r, a.nmagic, a.nshift), j = r - i * (uint32_t)N;
-      double acc = 0.0;
-      for (int c = 0; c < N; ++c) acc += Bm[i * N + c] * Bm[j * N + c];
-      Sm[r] = acc;
+    d4 M[TB][TB];
+    {
+      const double scale = 1.0 / t0;
+#pragma unroll
+      for (int r = 0; r < TB; ++r)
+#pragma unroll
+        for (int c = 0; c < TB; ++c) {
+          d4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+          for (int m = 0; m < TB; ++m)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+              acc = __builtin_amdgcn_mfma_f64_16x16x4f64(D[r][m][v], D[c][m][v], acc, 0, 0, 0);
+          M[r][c] = acc * scale;
+        }
     }
-    __syncthreads();
-    // Jacobi sweeps in tournament order: round r pairs the elements at
-    // positions i and n2 - 1 - i of the circle (element 0 fixed, the others
-    // rotated by r), so the N/2 rotations of a round touch disjoint rows and
-    // columns and are applied together (an odd N gets a dummy partner)
-    const int n2 = (N + 1) & ~1;
-    for (int sweep = 0; sweep < kMccSweeps; ++sweep) {
-      double off = 0.0, dia = 0.0;
-      for (uint32_t r = lane; r < NN; r += 64) {
-        const uint32_t i = divide(r, a.nmagic, a.nshift), j = r - i * (uint32_t)N;
-        const double v = Sm[r];
-        if (i == j) dia += v * v; else off += v * v;
+    double fac = 1.0;  // lane j: s_j, of the last squaring f_j
+    int j = 0;
+    for (;; ++j) {
+      double f = 0.0;
+#pragma unroll
+      for (int r = 0; r < TB; ++r)
+#pragma unroll
+        for (int c = 0; c < TB; ++c)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) f = fma(M[r][c][v], M[r][c][v], f);
+      f = wave_sum(f);
+      if (!(1.0 - f > kMccTol) || j + 1 == kMccSquarings) {  // (the same value on every lane)
+        fac = lane == j ? f : fac;
+        break;
       }
-      off = wave_sum_f64(off);
-      dia = wave_sum_f64(dia);
-      // off-diagonal norm below 1e-13 of the diagonal's: the eigenvalues then
-      // carry an error of order 1e-26 of the largest (second order in the
-      // off-diagonal part); the same decision on every lane
-      if (!(off > 1e-26 * dia)) break;
-      for (int round = 0; round < n2 - 1; ++round) {
-        if (lane < n2 / 2) {
-          const int pa = lane, pb = n2 - 1 - lane;
-          const int p = pa == 0 ? 0 : (pa - 1 + round) % (n2 - 1) + 1;
-          const int q = (pb - 1 + round) % (n2 - 1) + 1;
-          double cs = 1.0, sn = 0.0;
-          if (p < N && q < N) {
-            const double apq = Sm[p * N + q];
-            if (apq != 0.0) {
-              const double tau = (Sm[q * N + q] - Sm[p * N + p]) / (2.0 * apq);
-              const double tt = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-              cs = 1.0 / sqrt(1.0 + tt * tt);
-              sn = tt * cs;
-            }
-          }
-          rp[lane] = p;
-          rq[lane] = q;
-          rc[lane] = cs;
-          rs[lane] = sn;
+      const double scale = __builtin_amdgcn_rcp(f);
+      fac = lane == j ? scale : fac;
+      d4 Q[TB][TB];
+#pragma unroll
+      for (int r = 0; r < TB; ++r)
+#pragma unroll
+        for (int c = 0; c < TB; ++c) {
+          d4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+          for (int m = 0; m < TB; ++m)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+              acc = __builtin_amdgcn_mfma_f64_16x16x4f64(M[m][r][v], M[m][c][v], acc, 0, 0, 0);
+          Q[r][c] = acc;
         }
-        __syncthreads();
-        if (lane < N) {  // columns p and q of every pair, row `lane`
-          for (int i = 0; i < n2 / 2; ++i) {
-            const int p = rp[i], q = rq[i];
-            if (p >= N || q >= N) continue;
-            const double cs = rc[i], sn = rs[i];
-            const double x = Sm[lane * N + p], y = Sm[lane * N + q];
-            Sm[lane * N + p] = cs * x - sn * y;
-            Sm[lane * N + q] = sn * x + cs * y;
-          }
-        }
-        __syncthreads();
-        if (lane < N) {  // rows p and q of every pair, column `lane`
-          for (int i = 0; i < n2 / 2; ++i) {
-            const int p = rp[i], q = rq[i];
-            if (p >= N || q >= N) continue;
-            const double cs = rc[i], sn = rs[i];
-            const double x = Sm[p * N + lane], y = Sm[q * N + lane];
-            Sm[p * N + lane] = cs * x - sn * y;
-            Sm[q * N + lane] = sn * x + cs * y;
-          }
-        }
-        __syncthreads();
-      }
+#pragma unroll
+      for (int r = 0; r < TB; ++r)
+#pragma unroll
+        for (int c = 0; c < TB; ++c) M[r][c] = Q[r][c] * scale;
     }
-    // the two largest diagonal entries: the first is 1 (eigenvector sqrt(px))
-    const double d = lane < N ? Sm[lane * N + lane] : -1.0;
-    double m1 = d;
-    for (int o = 32; o; o >>= 1) m1 = fmax(m1, __shfl_xor(m1, o));
-    const unsigned long long at = __ballot(d == m1);
-    const int first = __ffsll((long long)at) - 1;  // one lane holding the largest
-    double m2 = lane == first ? -1.0 : d;
-    for (int o = 32; o; o >>= 1) m2 = fmax(m2, __shfl_xor(m2, o));
-    if (lane == 0) a.out_f[k] = (float)sqrt(m2 > 0.0 ? m2 : 0.0);
-    __syncthreads();  // Bm, Sm, rx, ry are rewritten for the next matrix
+    // ln of the product, a factor per lane (one logarithm for all of them)
+    const double ln = wave_sum(ldexp(log(fac), -1 - lane) * (lane == j ? 1.0 : -1.0));
+    if (lane == 0) a.out_f[k] = (float)(sqrt(t0) * exp(0.5 * ln));
   }
 }
 
 }  // namespace
 
 hipError_t launch_haralick_mcc(const StatsArgs& a, hipStream_t stream) {
-  const size_t lds = (2 * (size_t)a.N * a.N + 2 * (size_t)a.N) * sizeof(double);
-  hipLaunchKernelGGL(k_haralick_mcc, dim3(grid_for(a.K)), dim3(64), (uint32_t)lds, stream, a);
+  const int want = (a.K + kMccWaves - 1) / kMccWaves;
+  const dim3 grid((unsigned)(want < 4096 ? want : 4096)), block(kMccThreads);
+  switch ((a.N + 15) / 16) {
+    case 1: hipLaunchKernelGGL(k_haralick_mcc<1>, grid, block, 0, stream, a); break;
+    case 2: hipLaunchKernelGGL(k_haralick_mcc<2>, grid, block, 0, stream, a); break;
+    case 3: hipLaunchKernelGGL(k_haralick_mcc<3>, grid, block, 0, stream, a); break;
+    case 4: hipLaunchKernelGGL(k_haralick_mcc<4>, grid, block, 0, stream, a); break;
+    default: return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 
