@@ -19,6 +19,10 @@ struct StatsArgs {
   float* out_f;        // normalised [K][N][N], averaged [K/m][N][N], statistics [K][13]
   int K, N, m;         // m: matrices per averaged group
   uint32_t nmagic, nshift;
+  // N > 32, normalised and averaged: workgroups per matrix (group) and words
+  // of the result each writes; vec: every matrix 16-byte aligned
+  uint32_t parts, share;
+  int vec;
 };
 constexpr int kHaralickStats = 13;
 constexpr int kHaralickMaxN = 1024;  // the marginal arrays (7 N doubles) fit the LDS
