@@ -295,8 +295,8 @@ GLCM_API int glcm_compute(glcm_plan_t plan, const void *img, int W, int H, int64
  * entropy (natural log), homogeneity (inverse difference moment,
  * 1/(1+(i-j)^2)), correlation.  p = P/T with T = sum of P[k].  T = 0 gives
  * five zeros; a row or column marginal with a single occupied level gives
- * correlation 1.  Energy, entropy and homogeneity are summed in fp32; the
- * contrast and the correlation come from exact integer moments (the contrast
+ * correlation 1.  Energy, entropy and homogeneity are fp32 terms summed in
+ * fp64; the contrast and the correlation come from exact integer moments (the contrast
  * as one fp64 quotient, the correlation's variances and covariance combined
  * in fp64).
  *

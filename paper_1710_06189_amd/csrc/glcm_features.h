@@ -1,5 +1,5 @@
-// Haralick statistics of one GLCM computed by a whole workgroup: shared by the
-// features kernel and the batch kernel.
+// Five Haralick statistics of one GLCM by a wavefront or a workgroup: shared by
+// the features kernel and the batch kernel.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -12,143 +12,150 @@ namespace glcm {
 namespace {
 
 // ---------------------------------------------------------------------------
-// Haralick statistics of one GLCM computed by a whole workgroup (blockDim a
-// multiple of 64, at most 1024).  Exact integer sums for the contrast
-// numerator and the correlation moments; fp32 for energy, entropy and
-// homogeneity; fp64 (from exact 128-bit integers) for the correlation.
-// Sums are reduced within each wavefront by lane exchanges, then across the
-// wavefronts through LDS: three barriers in all.  redu: 7 blockDim / 64
-// words, redf: 3 blockDim / 64 words of workgroup scratch.  Every thread of
-// the workgroup must call it.
+// Five Haralick statistics of one GLCM.  Exact integer sums for the contrast
+// and the correlation moments; fp32 terms, added in fp64, for energy, entropy
+// and homogeneity; fp64 (from exact 128-bit integers) for the correlation.
+//
+// The bins are walked by W wavefronts.  A wavefront takes R = 64 / N whole rows
+// at a time (64 columns of one row when N > 64) and a lane keeps its column, so
+// sum c, sum i c and sum i^2 c per column are all the integers a bin adds to;
+// the rest follows once at the end (sum j c = j sum c and so on, and
+// sum (i - j)^2 c = sum i^2 c + sum j^2 c - 2 sum i j c).  The fp64 sums of a
+// wavefront meet by lane exchanges and those of the W wavefronts are added in
+// order, so the result depends on W, not on which wavefronts did the work: one
+// wavefront that plays all W (glcm_features_wave) gives the same bits as W of
+// them (glcm_features_wg).
 // ---------------------------------------------------------------------------
+constexpr int features_waves(int N) { return N <= 32 ? 1 : (N <= 128 ? 4 : 16); }
+
+struct FeatureSums {
+  unsigned long long si, sii, sij, sj, sjj;
+  double energy, ent, homog;
+};
+
 // The five statistics from the exact integer sums and the fp32 sums.
-__device__ __forceinline__ void features_store(unsigned long long T, unsigned long long sc, unsigned long long si,
-                                               unsigned long long sj, unsigned long long sii, unsigned long long sjj,
-                                               unsigned long long sij, float energy, float ent, float homog,
-                                               float* o) {
+__device__ __forceinline__ void features_store(unsigned long long T, const FeatureSums& s, float* o) {
   using i128 = __int128;
   const i128 tT = (i128)T;
-  const i128 vi = (i128)sii * tT - (i128)si * (i128)si;  // T^2 var_i
-  const i128 vj = (i128)sjj * tT - (i128)sj * (i128)sj;  // T^2 var_j
-  const i128 cv = (i128)sij * tT - (i128)si * (i128)sj;  // T^2 cov
+  const i128 vi = (i128)s.sii * tT - (i128)s.si * (i128)s.si;  // T^2 var_i
+  const i128 vj = (i128)s.sjj * tT - (i128)s.sj * (i128)s.sj;  // T^2 var_j
+  const i128 cv = (i128)s.sij * tT - (i128)s.si * (i128)s.sj;  // T^2 cov
+  const unsigned long long sc = s.sii + s.sjj - 2ull * s.sij;
   double corr = 1.0;
   if (vi != 0 && vj != 0) corr = (double)cv / sqrt((double)vi * (double)vj);
   o[0] = (float)((double)sc / (double)T);
-  o[1] = energy;
-  o[2] = ent;
-  o[3] = homog;
+  o[1] = (float)s.energy;
+  o[2] = (float)s.ent;
+  o[3] = (float)s.homog;
   o[4] = (float)corr;
 }
 
-__device__ __forceinline__ void glcm_features_wg(const uint32_t* P, uint32_t N, float* o, unsigned long long* redu, float* redf) {
-  const uint32_t NN = N * N, nw = blockDim.x >> 6, w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  // pass 1: total (needed for p)
+// Total of the matrix over one wavefront's share of the words (w of W).
+__device__ __forceinline__ unsigned long long features_total(const uint32_t* P, uint32_t NN, uint32_t w, uint32_t W) {
   unsigned long long T = 0;
-  for (uint32_t t = threadIdx.x; t < NN; t += blockDim.x) T += P[t];
-  T = wave_sum(T);
+#pragma unroll 8
+  for (uint32_t r = 64u * w + (threadIdx.x & 63u); r < NN; r += 64u * W) T += P[r];
+  return wave_sum(T);
+}
+
+// The sums of wavefront w of W (T below 2^32).
+__device__ __forceinline__ FeatureSums features_sums(const uint32_t* P, uint32_t N, unsigned long long T, float invT,
+                                                     uint32_t w, uint32_t W) {
+  const uint32_t lane = threadIdx.x & 63u;
+  const uint32_t R = N <= 64u ? 64u / N : 1u;
+  const uint32_t i0 = N <= 64u ? lane / N : 0u, jl = N <= 64u ? lane - i0 * N : lane;
+  FeatureSums s = {0, 0, 0, 0, 0, 0.0, 0.0, 0.0};
+  constexpr uint32_t U = 4;  // loads in flight
+  for (uint32_t j = jl; j - jl < N; j += 64u) {  // (the same trip count on every lane)
+    const bool live = i0 < R && j < N;
+    uint32_t col = 0;  // (sums of a column stay below T)
+    unsigned long long ci = 0, cii = 0;
+    for (uint32_t t = w * R; t < N; t += U * W * R) {
+      uint32_t c[U];
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) {
+        const uint32_t i = t + u * W * R + i0;
+        c[u] = live && i < N ? P[(size_t)i * N + j] : 0u;
+      }
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) {
+        if (c[u] == 0u) continue;
+        const uint32_t i = t + u * W * R + i0;
+        col += c[u];
+        ci += (unsigned long long)i * c[u];
+        cii += (unsigned long long)(i * i) * c[u];
+        const float p = (float)c[u] * invT;
+        s.energy += (double)(p * p);
+        // -p ln p; for p > 1/2 use log1p of the exact complement to keep accuracy
+        const float lp = (2ull * c[u] > T) ? log1pf(-(float)(T - c[u]) * invT) : logf(p);
+        s.ent -= (double)(p * lp);
+        const uint32_t d = i > j ? i - j : j - i;
+        s.homog += (double)(p / (1.0f + (float)(d * d)));
+      }
+    }
+    s.si += ci;
+    s.sii += cii;
+    s.sij += (unsigned long long)j * ci;
+    s.sj += (unsigned long long)j * col;
+    s.sjj += (unsigned long long)(j * j) * col;
+  }
+  s.si = wave_sum(s.si);
+  s.sii = wave_sum(s.sii);
+  s.sij = wave_sum(s.sij);
+  s.sj = wave_sum(s.sj);
+  s.sjj = wave_sum(s.sjj);
+  s.energy = wave_sum(s.energy);
+  s.ent = wave_sum(s.ent);
+  s.homog = wave_sum(s.homog);
+  return s;
+}
+
+__device__ __forceinline__ void features_add(FeatureSums& a, const FeatureSums& b) {
+  a.si += b.si; a.sii += b.sii; a.sij += b.sij; a.sj += b.sj; a.sjj += b.sjj;
+  a.energy += b.energy; a.ent += b.ent; a.homog += b.homog;
+}
+
+// By a workgroup of W wavefronts (W = features_waves(N)): two barriers.  redu:
+// W totals, reds: W sums of workgroup scratch.  Every thread of the workgroup
+// must call it.
+template <int W>
+__device__ __forceinline__ void glcm_features_wg(const uint32_t* P, uint32_t N, float* o, unsigned long long* redu,
+                                                 FeatureSums* reds) {
+  const uint32_t w = threadIdx.x >> 6, lane = threadIdx.x & 63u;
+  unsigned long long T = features_total(P, N * N, w, W);
   if (lane == 0) redu[w] = T;
   __syncthreads();
   T = 0;
-  for (uint32_t x = 0; x < nw; ++x) T += redu[x];
+#pragma unroll
+  for (int x = 0; x < W; ++x) T += redu[x];
   if (T == 0 || T > 0xffffffffull) {
     if (threadIdx.x < 5) o[threadIdx.x] = T == 0 ? 0.0f : __builtin_nanf("");
-    __syncthreads();
     return;
   }
-  const float invT = 1.0f / (float)T;
-  unsigned long long sc = 0, si = 0, sj = 0, sii = 0, sjj = 0, sij = 0;
-  float energy = 0.f, ent = 0.f, homog = 0.f;
-  // bin t = i N + j; (i, j) step by blockDim's digits in base N
-  const uint32_t di = blockDim.x / N, dj = blockDim.x % N;
-  uint32_t i = threadIdx.x / N, j = threadIdx.x % N;
-  for (uint32_t t = threadIdx.x; t < NN; t += blockDim.x) {
-    const uint32_t c = P[t];
-    if (c != 0) {
-      const unsigned long long d = i > j ? i - j : j - i;
-      sc += d * d * c;
-      si += (unsigned long long)i * c; sj += (unsigned long long)j * c;
-      sii += (unsigned long long)i * i * c; sjj += (unsigned long long)j * j * c;
-      sij += (unsigned long long)i * j * c;
-      const float p = (float)c * invT;
-      energy += p * p;
-      // -p ln p; for p > 1/2 use log1p of the exact complement to keep accuracy
-      const float lp = (2ull * c > T) ? log1pf(-(float)(T - c) * invT) : logf(p);
-      ent -= p * lp;
-      homog += p / (1.0f + (float)(d * d));
-    }
-    j += dj;
-    i += di;
-    if (j >= N) {
-      j -= N;
-      ++i;
-    }
-  }
-  sc = wave_sum(sc); si = wave_sum(si); sj = wave_sum(sj);
-  sii = wave_sum(sii); sjj = wave_sum(sjj); sij = wave_sum(sij);
-  energy = wave_sum(energy); ent = wave_sum(ent); homog = wave_sum(homog);
-  unsigned long long* ru = redu + nw;  // the totals above stay readable
-  if (lane == 0) {
-    ru[6 * w + 0] = sc; ru[6 * w + 1] = si; ru[6 * w + 2] = sj;
-    ru[6 * w + 3] = sii; ru[6 * w + 4] = sjj; ru[6 * w + 5] = sij;
-    redf[3 * w + 0] = energy; redf[3 * w + 1] = ent; redf[3 * w + 2] = homog;
-  }
+  const FeatureSums s = features_sums(P, N, T, 1.0f / (float)T, w, W);
+  if (lane == 0) reds[w] = s;
   __syncthreads();
   if (threadIdx.x == 0) {
-    sc = si = sj = sii = sjj = sij = 0;
-    energy = ent = homog = 0.f;
-    for (uint32_t x = 0; x < nw; ++x) {
-      sc += ru[6 * x + 0]; si += ru[6 * x + 1]; sj += ru[6 * x + 2];
-      sii += ru[6 * x + 3]; sjj += ru[6 * x + 4]; sij += ru[6 * x + 5];
-      energy += redf[3 * x + 0]; ent += redf[3 * x + 1]; homog += redf[3 * x + 2];
-    }
-    features_store(T, sc, si, sj, sii, sjj, sij, energy, ent, homog, o);
+    FeatureSums a = {0, 0, 0, 0, 0, 0.0, 0.0, 0.0};
+    for (int x = 0; x < W; ++x) features_add(a, reds[x]);
+    features_store(T, a, o);
   }
-  __syncthreads();  // the scratch may be reused once every thread is past it
 }
 
-// The same statistics computed by one wavefront, with no LDS and no barrier:
-// bit for bit what glcm_features_wg gives in a workgroup of one wavefront
-// (there the sums of the single wavefront are added to zero, which changes
-// nothing).  Every lane must call it; lane 0 writes o.
+// By one wavefront that plays all of features_waves(N), with no LDS and no
+// barrier.  Every lane must call it; lane 0 writes o.
 __device__ __forceinline__ void glcm_features_wave(const uint32_t* P, uint32_t N, float* o) {
-  const uint32_t NN = N * N, lane = threadIdx.x & 63;
-  unsigned long long T = 0;
-  for (uint32_t t = lane; t < NN; t += 64u) T += P[t];
-  T = wave_sum(T);
+  const uint32_t lane = threadIdx.x & 63u;
+  const uint32_t W = (uint32_t)features_waves((int)N);
+  const unsigned long long T = features_total(P, N * N, 0, 1);
   if (T == 0 || T > 0xffffffffull) {
     if (lane < 5) o[lane] = T == 0 ? 0.0f : __builtin_nanf("");
     return;
   }
   const float invT = 1.0f / (float)T;
-  unsigned long long sc = 0, si = 0, sj = 0, sii = 0, sjj = 0, sij = 0;
-  float energy = 0.f, ent = 0.f, homog = 0.f;
-  const uint32_t di = 64u / N, dj = 64u % N;
-  uint32_t i = lane / N, j = lane % N;
-  for (uint32_t t = lane; t < NN; t += 64u) {
-    const uint32_t c = P[t];
-    if (c != 0) {
-      const unsigned long long d = i > j ? i - j : j - i;
-      sc += d * d * c;
-      si += (unsigned long long)i * c; sj += (unsigned long long)j * c;
-      sii += (unsigned long long)i * i * c; sjj += (unsigned long long)j * j * c;
-      sij += (unsigned long long)i * j * c;
-      const float p = (float)c * invT;
-      energy += p * p;
-      const float lp = (2ull * c > T) ? log1pf(-(float)(T - c) * invT) : logf(p);
-      ent -= p * lp;
-      homog += p / (1.0f + (float)(d * d));
-    }
-    j += dj;
-    i += di;
-    if (j >= N) {
-      j -= N;
-      ++i;
-    }
-  }
-  sc = wave_sum(sc); si = wave_sum(si); sj = wave_sum(sj);
-  sii = wave_sum(sii); sjj = wave_sum(sjj); sij = wave_sum(sij);
-  energy = wave_sum(energy); ent = wave_sum(ent); homog = wave_sum(homog);
-  if (lane == 0) features_store(T, sc, si, sj, sii, sjj, sij, 0.f + energy, 0.f + ent, 0.f + homog, o);
+  FeatureSums a = {0, 0, 0, 0, 0, 0.0, 0.0, 0.0};
+  for (uint32_t w = 0; w < W; ++w) features_add(a, features_sums(P, N, T, invT, w, W));
+  if (lane == 0) features_store(T, a, o);
 }
 
 }  // namespace

@@ -1,5 +1,5 @@
-// Haralick statistics kernel: one workgroup per GLCM (Section I; the five
-// statistics and their precision are described in glcm_features.h).
+// Haralick statistics kernels: a wavefront or a workgroup per GLCM (Section I;
+// the five statistics and their precision are described in glcm_features.h).
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -10,15 +10,16 @@
 namespace glcm {
 namespace {
 
-__global__ __launch_bounds__(256) void k_features(const uint32_t* glcm, int N, float* out) {
-  __shared__ unsigned long long redu[256];
-  __shared__ float redf[256];
-  glcm_features_wg(glcm + (size_t)blockIdx.x * (uint32_t)N * (uint32_t)N, (uint32_t)N, out + (size_t)blockIdx.x * 5,
-                   redu, redf);
+// N > 32: one workgroup of W wavefronts per GLCM.
+template <int W>
+__global__ __launch_bounds__(64 * W) void k_features(const uint32_t* glcm, int N, float* out) {
+  __shared__ unsigned long long redu[W];
+  __shared__ FeatureSums reds[W];
+  glcm_features_wg<W>(glcm + (size_t)blockIdx.x * (uint32_t)N * (uint32_t)N, (uint32_t)N,
+                      out + (size_t)blockIdx.x * 5, redu, reds);
 }
 
-// N <= kFeaturesWaveMaxN: one wavefront per GLCM, four per workgroup (the
-// batch kernel takes its statistics the same way, so both agree bit for bit).
+// N <= 32: one wavefront per GLCM, four per workgroup.
 __global__ __launch_bounds__(256) void k_features_wave(const uint32_t* glcm, int K, int N, float* out) {
   const int k = blockIdx.x * 4 + (int)(threadIdx.x >> 6);
   if (k >= K) return;
@@ -28,10 +29,11 @@ __global__ __launch_bounds__(256) void k_features_wave(const uint32_t* glcm, int
 }  // namespace
 
 hipError_t launch_features(const uint32_t* glcm, int K, int N, float* out, hipStream_t stream) {
-  if (N <= kFeaturesWaveMaxN)
-    hipLaunchKernelGGL(k_features_wave, dim3((K + 3) / 4), dim3(256), 0, stream, glcm, K, N, out);
-  else
-    hipLaunchKernelGGL(k_features, dim3(K), dim3(256), 0, stream, glcm, N, out);
+  switch (features_waves(N)) {
+    case 1: hipLaunchKernelGGL(k_features_wave, dim3((K + 3) / 4), dim3(256), 0, stream, glcm, K, N, out); break;
+    case 4: hipLaunchKernelGGL(k_features<4>, dim3(K), dim3(256), 0, stream, glcm, N, out); break;
+    default: hipLaunchKernelGGL(k_features<16>, dim3(K), dim3(1024), 0, stream, glcm, N, out); break;
+  }
   return hipGetLastError();
 }
 

@@ -183,8 +183,7 @@ hipError_t launch_vote_global(const VoteArgs& a, int dtype_bytes, hipStream_t st
 // in runs of a.region_rows; `groups` workgroups of 256 threads.
 hipError_t launch_vote_l2(const VoteArgs& a, int dtype_bytes, int groups, hipStream_t stream,
                           const LaunchTiming& tm = {});
-// Statistics of K GLCMs: one wavefront per GLCM up to this N, one workgroup above.
-constexpr int kFeaturesWaveMaxN = 128;
+// Statistics of K GLCMs.
 hipError_t launch_features(const uint32_t* glcm, int K, int N, float* out, hipStream_t stream);
 // Block-code kernel: a.nregions workgroups of `wg` threads, block_lds_bytes(N, a.fb_copies) of LDS.
 hipError_t launch_vote_blocks(const BlockArgs& a, int dtype_bytes, int wg, hipStream_t stream,
