@@ -105,8 +105,9 @@ typedef struct glcm_tuning {
     int tile_rows;      /* host-image upload tile height (rows) */
     int counter_bits;   /* LDS counters: 16 or 32; 0 keeps the current value.  Slab kernel:
                            two copies per dword; strip kernel: two GLCMs per dword (dwords
-                           per bin 4, 8, 16 or 32); partitioned kernel: two bins per dword
-                           with one copy (replicas 1), bands then kept below 2^16 pixels.
+                           per bin 4, 8, 16 or 32); partitioned path: two bins per dword
+                           with one copy (replicas 1), a workgroup then holding a slice of
+                           one GLCM's rows and emptying bins before they can overflow.
                            16-bit layouts are used only where no count can overflow */
     int merge;          /* 0: workgroups add their counts into per-XCD accumulators in L2,
                            a small kernel sums the 8 slices; 1: per-band partial counts,

@@ -16,6 +16,7 @@
 #include "glcm_host.h"
 #include "glcm_internal.h"
 #include "glcm_hist.h"
+#include "glcm_levels.h"
 
 using glcm::VoteArgs;
 
@@ -205,6 +206,7 @@ struct glcm_plan_s {
   uint32_t* xbuf = nullptr;  // [kXcdSlots][K*N*N] accumulation slices, kept zero between calls
   uint32_t xslots = glcm::kXcdSlots;  // slices the device's XCC_IDs reach (the rest stay zero)
   bool no_alloc = false;  // a transient plan of compute_in_workspace: never allocate (no staging copy)
+  size_t partials_cap = SIZE_MAX;  // most bytes of partials the plan may hold (glcm::limit_partials)
 
 
   // ordering across streams
@@ -400,6 +402,51 @@ bool blocks_fit(const glcm_plan_s* p) {
   for (int k = 0; k < p->K; ++k)
     if (block_glcm(p->offsets[k]) < 0) return false;
   return true;
+}
+
+// The partitioned path counts with the level-slice kernel (glcm_levels.hip)
+// where its bins are 16-bit: several partitions of one copy each.  Measured on
+// MI355X, 4096^2 u8, per call against ranges of 16-bit bins that each walked
+// the whole image and merged through L2 atomics (smooth; noise; constant):
+// N = 256 with 12 offsets 120; 118; 307 us against 459; 1178; 875, with one
+// offset 38; 38; 107 against 82; 158; 131, N = 1024 with 2 offsets 76; 76; 169
+// against 1064; 1132; 1133 (256 values counted), N = 128 with 12 offsets beyond
+// the row kernels' reach 113; 111; 266 against 297; 425; 863.
+bool levels_plan(const glcm_plan_s* p) {
+  const glcm_tuning_t& t = p->tuning;
+  return (t.path == kPathGeneric || t.path == kPathPartitioned) && t.counter_bits == 16 && t.partitions >= 2 &&
+         t.replicas == 1 && t.merge == 0 && p->xbuf != nullptr;
+}
+
+// Layout of the level-slice kernel for rows [y_begin, y_end) of a W x H image:
+// slices of whole rows of a GLCM of `levels` levels that fit the LDS, and bands
+// so that the workgroups fill the CUs once, each with at least two steps of
+// pairs.
+struct LevelLayout {
+  int slices = 1, bands = 1;
+  uint32_t slice_rows = 0, slice_dwords = 0, spill_cap = 0;
+  uint64_t units = 0, row_words = 0;  // (offset, slice) pairs; words of partials a workgroup owns
+  uint64_t bytes() const { return units * (uint64_t)bands * row_words * 4u; }
+};
+
+LevelLayout level_layout(const glcm_plan_s* p, int levels, int W, int rows) {
+  LevelLayout L;
+  const uint64_t N = (uint64_t)levels, pitch = glcm::level_pitch((uint32_t)levels);
+  const uint64_t most = (uint64_t)p->lds_budget_words / pitch;  // levels per slice
+  const uint64_t S0 = (N + most - 1) / most;
+  L.slice_rows = (uint32_t)((N + S0 - 1) / S0);
+  L.slices = (int)((N + L.slice_rows - 1) / L.slice_rows);
+  L.slice_dwords = (uint32_t)(((uint64_t)L.slice_rows * pitch + 3) & ~3ull);
+  L.units = (uint64_t)p->K * (uint64_t)L.slices;
+  const uint64_t chunks = (((uint64_t)W + 15) / 16) * (uint64_t)rows;
+  const uint64_t per_cu = std::max<uint64_t>(1, std::min<uint64_t>(2, (uint64_t)p->lds_budget_words / L.slice_dwords));
+  uint64_t bands = std::max<uint64_t>(1, (uint64_t)std::max(1, p->num_cus) * per_cu / L.units);
+  bands = std::min(bands, std::max<uint64_t>(1, chunks / (2 * glcm::kLevelThreads)));
+  L.bands = (int)bands;
+  // a spill takes 2^15 of a workgroup's pairs (at most 16 per chunk)
+  L.spill_cap = (uint32_t)((chunks / bands + 1) * 16 / 32768 + 1);
+  L.row_words = (uint64_t)L.slice_dwords + 1 + L.spill_cap;
+  return L;
 }
 
 // Image passes of the partitioned kernel worth one GLCM's pairs added into
@@ -644,6 +691,100 @@ int record_done(glcm_plan_t p, hipStream_t s) {
   return GLCM_OK;
 }
 
+// Makes room for the level-slice kernel's partials (bytes for this call):
+// false when the plan may not hold them, or would have to allocate while
+// `stream` is being captured; *rc is then GLCM_OK, or the HIP failure.
+bool level_partials(glcm_plan_t p, size_t bytes, hipStream_t stream, int* rc) {
+  *rc = GLCM_OK;
+  if (bytes <= p->partials_bytes) return true;
+  if (bytes > p->partials_cap) return false;
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    return false;
+  }
+  *rc = ensure_partials(p, bytes);
+  return *rc == GLCM_OK;
+}
+
+// Counts rows [y_begin, y_end) with the level-slice kernel into out.
+// *done = false (and nothing queued): the plan has no room for its partials.
+int count_levels(glcm_plan_t p, const VoteArgs& v, int b, uint32_t* out, bool accumulate, hipStream_t stream,
+                 bool* done) {
+  *done = false;
+  // fewer values than levels: counted by value (one slice), spread by the sum;
+  // only where no pixel lies above hi (its level, N - 1, has no value)
+  const uint32_t values = v.q.hi - v.q.lo + 1u, top = b == 1 ? 255u : 65535u;
+  uint32_t counted = (uint32_t)p->N;
+  LevelLayout L = level_layout(p, p->N, v.W, v.y_end - v.y_begin);
+  if (values < counted && v.q.hi == top) {
+    const LevelLayout by_value = level_layout(p, (int)values, v.W, v.y_end - v.y_begin);
+    if (by_value.slices == 1) {
+      L = by_value;
+      counted = values;
+    }
+  }
+  uint32_t* mem = nullptr;
+  if (p->no_alloc) {
+    // the caller's accumulation slices serve as partials (no other kernel of
+    // this call uses them)
+    const uint64_t room = (uint64_t)glcm::kXcdSlots * v.words_total * 4u;
+    if (L.bytes() > room) L.bands = (int)std::max<uint64_t>(1, room / (L.bytes() / (uint64_t)L.bands));
+    const uint64_t chunks = (((uint64_t)v.W + 15) / 16) * (uint64_t)(v.y_end - v.y_begin);
+    for (; L.bands >= 1; --L.bands) {  // fewer bands have longer spill lists
+      L.spill_cap = (uint32_t)((chunks / (uint64_t)L.bands + 1) * 16 / 32768 + 1);
+      L.row_words = (uint64_t)L.slice_dwords + 1 + L.spill_cap;
+      if (L.bytes() <= room) break;
+    }
+    if (L.bands < 1) return GLCM_OK;
+    mem = p->xbuf;
+  } else {
+    int rc = GLCM_OK;
+    if (!level_partials(p, (size_t)L.bytes(), stream, &rc)) return rc;
+    mem = p->partials;
+  }
+  glcm::LevelArgs a;
+  std::memset(&a, 0, sizeof(a));
+  a.img = v.img;
+  a.stride = v.stride;
+  a.W = v.W;
+  a.H = v.H;
+  a.y_begin = v.y_begin;
+  a.y_end = v.y_end;
+  a.N = (uint32_t)p->N;
+  a.q = make_quant((int)counted, v.q.lo, v.q.hi);
+  fast_quant(b, (int)counted, v.q.lo, v.q.hi, &a.qfast, &a.qfast_shift, &a.qfast_mask);
+  a.div_n = make_quant(1, 0, a.N - 1);
+  a.div_values = make_quant(1, 0, counted - 1);
+  a.K = p->K;
+  for (int k = 0; k < p->K; ++k) {
+    a.dx[k] = p->offsets[k].dx;
+    a.dy[k] = p->offsets[k].dy;
+  }
+  a.slices = L.slices;
+  a.slice_rows = L.slice_rows;
+  a.pitch = glcm::level_pitch(counted);
+  a.slice_dwords = L.slice_dwords;
+  a.div_pitch = make_quant(1, 0, a.pitch - 1);
+  a.bands = L.bands;
+  const uint64_t rows = L.units * (uint64_t)L.bands;
+  a.partials = mem;
+  a.spill_count = mem + rows * L.slice_dwords;
+  a.spills = a.spill_count + rows;
+  a.spill_cap = L.spill_cap;
+  a.out = out;
+  a.accumulate = accumulate ? 1 : 0;
+  glcm::LaunchTiming tm;
+  if (p->flags & GLCM_FLAG_TIMING) {
+    GLCM_TRY(hipEventCreate(&tm.start));
+    GLCM_TRY(hipEventCreate(&tm.stop));
+    p->timing.emplace_back(tm.start, tm.stop);
+  }
+  *done = true;
+  GLCM_TRY(glcm::launch_vote_levels(a, b, stream, tm));
+  return GLCM_OK;
+}
+
 // Queues the counting of first-pixel rows [y_begin, y_end) of a device image
 // whose rows [0, H) are all resident, writing (or adding into) out.
 // finish = false leaves the counts in the per-XCD accumulators (host tiles);
@@ -801,17 +942,13 @@ int count_device(glcm_plan_t p, const void* img, int W, int H, int64_t stride, i
     R = 1;
     while (R < 16 && ((uint64_t)words * 2 * R + budget - 1) / budget <= (uint64_t)P) R *= 2;
   }
-  // generic kernel over two or more bin partitions with one copy: 16-bit
-  // counters, two words per dword, halve the partitions (each band is then
-  // kept below 2^16 first pixels, the most one counter can receive, which
-  // needs rows of at most 65535 pixels)
-  bool g16 = false;
+  // two or more bin partitions with one copy of 16-bit bins: level slices
+  // (where the plan has no room for their partials, ranges of 32-bit bins)
   if ((path == kPathGeneric || path == kPathPartitioned) && t.counter_bits == 16 && P >= 2 && R == 1 && xcd &&
-      W <= 65535) {
-    const uint64_t budget = (uint64_t)p->lds_budget_words;
-    const int P16 = (int)(((uint64_t)words + 2 * budget - 1) / (2 * budget));
-    P = (p->flags & GLCM_FLAG_FORCE_PARTITIONED) ? std::max(P16, P) : P16;  // forced: keep the passes
-    g16 = true;
+      finish) {
+    bool done = false;
+    const int rc = count_levels(p, a, b, out, accumulate, stream, &done);
+    if (done || rc != GLCM_OK) return rc;
   }
   int log2R = 0;
   while ((1 << log2R) < R) ++log2R;
@@ -862,8 +999,7 @@ int count_device(glcm_plan_t p, const void* img, int W, int H, int64_t stride, i
                  : path == kPathRows ? std::min(t.wg_size, glcm::rows_max_threads(b, c.maxdy, a.unaligned != 0))
                                      : t.wg_size;
   const int nwaves = wg / 64;
-  if (g16) a.c16 = 1;
-  size_t lds_need = g16 ? (size_t)((a.part_words + 1u) / 2u) * 4u : ((size_t)a.part_words << log2R) * 4u;
+  size_t lds_need = ((size_t)a.part_words << log2R) * 4u;
   if (path == kPathRows)
     lds_need = (size_t)(a.part_words / NN) * row_glcm_dwords(p->N, R, t.counter_bits == 16 ? 16 : 32) * 4u;
   lds_need = std::max(lds_need, (size_t)wg * 4u);
@@ -879,10 +1015,6 @@ int count_device(glcm_plan_t p, const void* img, int W, int H, int64_t stride, i
     region_rows = sl.region_rows;
     a.strip_rows = sl.strip_rows;
   }
-  if (g16 && (uint64_t)region_rows * (uint64_t)W > 65535u) {
-    region_rows = std::max(1, 65535 / W);
-    nregions = (rows + region_rows - 1) / region_rows;
-  }
   a.nregions = nregions;
   a.region_rows = region_rows;
   a.rows_per_wave = rpw;
@@ -896,7 +1028,7 @@ int count_device(glcm_plan_t p, const void* img, int W, int H, int64_t stride, i
   }
 
   // LDS: the copies (at least one word per thread)
-  size_t lds_bytes = g16 ? (size_t)((a.part_words + 1u) / 2u) * 4u : ((size_t)a.part_words << log2R) * 4u;
+  size_t lds_bytes = ((size_t)a.part_words << log2R) * 4u;
   if (path == kPathRows) {
     // 16-bit counters only when no count can reach 2^16: each slab gives a
     // copy at most 64 lanes / R x 16 pixels x 4 rows votes into one bin.
@@ -1021,7 +1153,8 @@ int count_host(glcm_plan_t p, const void* img, bool pinned, int W, int H, int64_
     p->pin_pending[s] = !pinned;
     if (!serial) GLCM_TRY(hipStreamWaitEvent(stream, p->uploaded[s], 0));
     const bool last = r1 >= H;
-    const bool xcd = p->tuning.merge == 0 && p->xbuf != nullptr;
+    // (the level-slice kernel keeps nothing in the slices: its tiles add to out)
+    const bool xcd = p->tuning.merge == 0 && p->xbuf != nullptr && !levels_plan(p);
     int rc = count_device(p, dev, W, rows, (int64_t)(pitch_bytes / b), r0 - ra, r1 - ra, lo, hi, out,
                           xcd ? false : tile > 0, xcd ? last : true, stream);
     if (rc != GLCM_OK) return rc;
@@ -1187,8 +1320,11 @@ GLCM_API int glcm_offset_polar(int d, int theta_deg, glcm_offset_t* out) {
   return GLCM_OK;
 }
 
-GLCM_API int glcm_plan_create(glcm_plan_t* plan, int dtype, int N, int K, const glcm_offset_t* offsets, int max_W,
-                     int max_H, uint32_t flags) {
+extern "C++" {
+namespace glcm {
+
+int create_plan(glcm_plan_t* plan, int dtype, int N, int K, const glcm_offset_t* offsets, int max_W, int max_H,
+                uint32_t flags) {
   if (!plan) return GLCM_EINVAL;
   *plan = nullptr;
   if (dtype_bytes(dtype) == 0 || N < 1 || N > GLCM_MAX_LEVELS) return GLCM_EINVAL;
@@ -1212,6 +1348,34 @@ GLCM_API int glcm_plan_create(glcm_plan_t* plan, int dtype, int N, int K, const 
   }
   *plan = p.release();
   return GLCM_OK;
+}
+
+void limit_partials(glcm_plan_t plan, size_t more_bytes) {
+  std::lock_guard<std::mutex> lk(plan->mu);
+  plan->partials_cap = more_bytes > SIZE_MAX - plan->partials_bytes ? SIZE_MAX : plan->partials_bytes + more_bytes;
+}
+
+}  // namespace glcm
+}  // extern "C++"
+
+GLCM_API int glcm_plan_create(glcm_plan_t* plan, int dtype, int N, int K, const glcm_offset_t* offsets, int max_W,
+                     int max_H, uint32_t flags) {
+  int rc = glcm::create_plan(plan, dtype, N, K, offsets, max_W, max_H, flags);
+  if (rc != GLCM_OK || !levels_plan(*plan)) return rc;
+  // the partials of the largest image, so that no call allocates them (also
+  // enough for fewer offsets: the workgroups of a call fill the CUs at most
+  // once unless K alone is more)
+  const LevelLayout L = level_layout(*plan, N, max_W, max_H);
+  const uint64_t per_cu = std::max<uint64_t>(1, std::min<uint64_t>(2, (uint64_t)(*plan)->lds_budget_words / L.slice_dwords));
+  const uint64_t groups = std::max<uint64_t>(L.units * (uint64_t)L.bands,
+                                             std::min<uint64_t>((uint64_t)(*plan)->num_cus * per_cu,
+                                                                L.units * (uint64_t)L.bands * 2));
+  rc = ensure_partials(*plan, (size_t)(groups * L.row_words * 4u));
+  if (rc != GLCM_OK) {
+    (void)glcm_plan_destroy(*plan);
+    *plan = nullptr;
+  }
+  return rc;
 }
 
 GLCM_API int glcm_plan_tuning(glcm_plan_t plan, glcm_tuning_t* tuning, int set) {
@@ -1567,7 +1731,7 @@ GLCM_API int glcm_compute(glcm_plan_t plan, const void* img, int W, int H, int64
     }
     rc = plan_cache().acquire(
         std::make_tuple(cur, dtype, N, K, key),
-        [&](glcm_plan_t* np) { return glcm_plan_create(np, dtype, N, K, offsets, 65535, 65535, 0); }, &plan);
+        [&](glcm_plan_t* np) { return glcm::create_plan(np, dtype, N, K, offsets, 65535, 65535, 0); }, &plan);
     if (rc != GLCM_OK) return rc;
     cached.plan = plan;
   }
@@ -2009,7 +2173,7 @@ GLCM_API int glcm_histogram(glcm_plan_t plan, const void* img, int W, int H, int
     rc = plan_cache().acquire(
         std::make_tuple(cur, dtype, N, 0, std::vector<int32_t>{}),
         [&](glcm_plan_t* np) {
-          return glcm_plan_create(np, dtype, N, 1, &kZero, 65535, 65535, GLCM_FLAG_FORCE_GLOBAL);
+          return glcm::create_plan(np, dtype, N, 1, &kZero, 65535, 65535, GLCM_FLAG_FORCE_GLOBAL);
         },
         &plan);
     if (rc != GLCM_OK) return rc;

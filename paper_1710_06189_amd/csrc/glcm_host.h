@@ -24,13 +24,22 @@ int memory_kind(const void* p, int* device);
 
 // glcm_compute on a device image without a plan and without allocating:
 // a plan lives on the stack for the call, its per-XCD accumulation slices are
-// `slices` (device memory of slice_words 32-bit words, any content on entry,
-// zero on return), misaligned images take the per-pixel kernels instead of a
+// `slices` (device memory of slice_words 32-bit words, any content on entry;
+// the call clears what it needs), misaligned images take the per-pixel kernels instead of a
 // staging copy.  GLCM_EINVAL when kXcdSlots * K * N * N > slice_words or
 // either pointer is not device memory of the current device.
 int compute_in_workspace(uint32_t* slices, size_t slice_words, const void* img, int W, int H, int64_t stride,
                          int dtype, int N, uint32_t lo, uint32_t hi, const glcm_offset_t* offsets, int K,
                          uint32_t* out, hipStream_t stream);
+
+// glcm_plan_create without the level-slice kernel's partials: calls that need
+// them allocate them, up to what limit_partials leaves.
+int create_plan(glcm_plan_t* plan, int dtype, int N, int K, const glcm_offset_t* offsets, int max_W, int max_H,
+                uint32_t flags);
+
+// The plan may add at most more_bytes to the partials it holds; a call that
+// would need more takes the kernel without them.
+void limit_partials(glcm_plan_t plan, size_t more_bytes);
 
 // glcm_batch_compute with a destination per image: image t's counts go to
 // outs[t] (device, K*N*N words) and its statistics to feats[t] (K*5 floats;

@@ -365,7 +365,7 @@ int launch(glcm_server_s* s, Admission& a) {
     // created for kcap offsets (the request's, repeated) and re-targeted below
     glcm_offset_t capo[GLCM_MAX_OFFSETS];
     for (int k = 0; k < a.kcap; ++k) capo[k] = q->offs[k % q->r.K];
-    int rc = glcm_plan_create(&plan, q->r.dtype, q->r.N, a.kcap, capo, kPlanMaxSide, kPlanMaxSide, 0);
+    int rc = glcm::create_plan(&plan, q->r.dtype, q->r.N, a.kcap, capo, kPlanMaxSide, kPlanMaxSide, 0);
     std::lock_guard<std::mutex> lk(s->mu);
     s->held -= plan_estimate(q->r.N, a.kcap);  // the estimate is replaced by what the plan holds
     if (rc != GLCM_OK) return rc;
@@ -392,6 +392,12 @@ int launch(glcm_server_s* s, Admission& a) {
   if (!plan) return GLCM_EINVAL;
   int rc = glcm_plan_rebind(plan, q->offs, q->r.K);
   if (rc != GLCM_OK) return rc;
+  {
+    // what the call may allocate beside what is held (only this thread admits,
+    // so nothing else takes it meanwhile)
+    std::lock_guard<std::mutex> lk(s->mu);
+    glcm::limit_partials(plan, s->budget > s->held ? (size_t)(s->budget - s->held) : 0);
+  }
   // (the group is fixed once admitted: only this thread reads it until the
   // launch completes)
   if (!q->group.empty()) {

@@ -576,7 +576,6 @@ __global__ __launch_bounds__(64 * W) void k_haralick(StatsArgs a) {
     double T = 0.0;
     for (int j0 = 0; j0 < N; j0 += 256) {
       double cs[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll 2
       for (int i = wave; i < N; i += W) {
         double s = 0.0;
 #pragma unroll

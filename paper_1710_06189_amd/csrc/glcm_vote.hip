@@ -79,31 +79,6 @@ __device__ void store_partial(const VoteArgs& a, const uint32_t* lds, uint32_t p
   }
 }
 
-// Merge of the generic kernel's 16-bit layout (word w in half w & 1 of dword
-// w >> 1, one copy): into the XCD slice or the band partial.
-__device__ void store_partial_bin_pairs(const VoteArgs& a, const uint32_t* lds, uint32_t pbase, uint32_t pwords,
-                                        int region) {
-  __syncthreads();
-  uint32_t* dst = a.partials + (size_t)region * a.words_total + pbase;
-  uint32_t xcc = 0;
-  if (a.xbuf) asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID, 0, 4)" : "=s"(xcc));
-  uint32_t* xs = a.xbuf + (size_t)(xcc & (kXcdSlots - 1u)) * a.words_total + pbase;
-  for (uint32_t m = threadIdx.x; 2u * m < pwords; m += blockDim.x) {
-    const uint32_t d = lds[m];
-#pragma unroll
-    for (uint32_t h = 0; h < 2; ++h) {
-      const uint32_t w = 2u * m + h;
-      if (w >= pwords) break;
-      const uint32_t s = (d >> (16u * h)) & 0xffffu;
-      if (a.xbuf) {
-        if (s) __hip_atomic_fetch_add(xs + w, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      } else {
-        dst[w] = s;
-      }
-    }
-  }
-}
-
 // out[w] = (accumulate ? out[w] : 0) + sum of the first nslots accumulation
 // slices (the others stay zero); clears them.
 __global__ __launch_bounds__(256) void k_finish(uint32_t* xbuf, uint32_t* out, uint32_t M, uint32_t nslots,
@@ -254,7 +229,6 @@ __device__ __forceinline__ void generic_votes(const VoteArgs& a, uint32_t* lds, 
   const uint32_t qs = (uint32_t)keep_s((int)a.qfast_shift);
   const Quant q{(uint32_t)keep_s((int)a.q.lo), (uint32_t)keep_s((int)a.q.hi), N, (uint32_t)keep_s((int)a.q.magic),
                 (uint32_t)keep_s((int)a.q.shift)};
-  const bool c16 = a.c16 != 0;
   const int log2R = keep_s(a.log2R);
   for (int y = y0 + ty; y < y1; y += tr) {
     const Pix* row = img + (int64_t)y * a.stride;
@@ -279,11 +253,7 @@ __device__ __forceinline__ void generic_votes(const VoteArgs& a, uint32_t* lds, 
         for (int j = 0; j < NK; ++j) {
           const uint32_t w = wbase[j] + av * N + (qf ? v2[u][j] >> qs : quantize(v2[u][j], q));
           if (ok[u][j] && w < pwords) {
-            if (c16)
-              __hip_atomic_fetch_add(&lds[w >> 1], 1u << ((w & 1u) << 4), __ATOMIC_RELAXED,
-                                     __HIP_MEMORY_SCOPE_WORKGROUP);
-            else
-              __hip_atomic_fetch_add(&lds[(w << log2R) + r], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            __hip_atomic_fetch_add(&lds[(w << log2R) + r], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
           }
         }
       }
@@ -298,9 +268,7 @@ __global__ __launch_bounds__(1024) void k_vote_generic(VoteArgs a) {
   const int region = rp.x, part = rp.y;
   const uint32_t pbase = (uint32_t)part * a.part_words;
   const uint32_t pwords = min(a.part_words, a.words_total - pbase);
-  // c16: 16-bit counters, words 2m and 2m + 1 in the low and high halves of
-  // dword m (one copy); the host keeps every band below 2^16 first pixels
-  zero_lds(lds, a.c16 ? (pwords + 1u) >> 1 : pwords << a.log2R);
+  zero_lds(lds, pwords << a.log2R);
   __syncthreads();
 
   const Pix* img = (const Pix*)a.img;
@@ -335,21 +303,12 @@ __global__ __launch_bounds__(1024) void k_vote_generic(VoteArgs a) {
         if ((unsigned)x2 >= (unsigned)a.W || (unsigned)y2 >= (unsigned)a.H) continue;
         const uint32_t v2 = img[(int64_t)y2 * a.stride + x2];
         const uint32_t w = row + (a.qfast ? v2 >> a.qfast_shift : quantize(v2, a.q)) - pbase;
-        if (w < pwords) {
-          if (a.c16)
-            __hip_atomic_fetch_add(&lds[w >> 1], 1u << ((w & 1u) << 4), __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_WORKGROUP);
-          else
-            __hip_atomic_fetch_add(&lds[(w << a.log2R) + r], 1u, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_WORKGROUP);
-        }
+        if (w < pwords)
+          __hip_atomic_fetch_add(&lds[(w << a.log2R) + r], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       }
     }
   }
-  if (a.c16)
-    store_partial_bin_pairs(a, lds, pbase, pwords, region);
-  else
-    store_partial(a, lds, pbase, pwords, region, a.q.nlev, a.q.nlev * a.q.nlev, false);
+  store_partial(a, lds, pbase, pwords, region, a.q.nlev, a.q.nlev * a.q.nlev, false);
 }
 
 // ---------------------------------------------------------------------------
