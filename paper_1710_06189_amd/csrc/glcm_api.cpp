@@ -17,6 +17,7 @@
 #include "glcm_internal.h"
 #include "glcm_hist.h"
 #include "glcm_levels.h"
+#include "glcm_onehot.h"
 
 using glcm::VoteArgs;
 
@@ -194,7 +195,7 @@ struct glcm_plan_s {
   int max_W = 0, max_H = 0;
   uint32_t flags = 0;
   glcm_tuning_t tuning{};
-  bool user_tuned = false;
+  bool user_tuned = false;  // launch parameters set or kept by the autotuner: the kernel they name runs
   int lds_budget_words = 0;
   int num_cus = 0;
 
@@ -447,6 +448,57 @@ LevelLayout level_layout(const glcm_plan_s* p, int levels, int W, int rows) {
   L.spill_cap = (uint32_t)((chunks / bands + 1) * 16 / 32768 + 1);
   L.row_words = (uint64_t)L.slice_dwords + 1 + L.spill_cap;
   return L;
+}
+
+// The matrix-core kernel (glcm_onehot.hip): up to 16 levels, every offset along
+// the four directions of Eq. (2) at d = 1, 2 or 4, on a plan that would take a
+// row kernel by default.  Reach 1, 2 or 4; 0 where it does not apply.
+int onehot_reach(const glcm_offset_t* offsets, int K, int N) {
+  if (N > glcm::kOnehotMaxN) return 0;
+  const Canon c = canonicalize(offsets, K);
+  int reach = 1;
+  for (int k = 0; k < K; ++k) {
+    if (glcm::onehot_slot(c.dx[k], c.dy[k]) < 0) return 0;
+    reach = std::max({reach, std::abs(c.dx[k]), c.dy[k]});
+  }
+  return reach;
+}
+
+// Where it beats the row kernels.  It counts all four directions of every
+// distance it has at a time that depends on the pixels alone, about 10 us and
+// 0.38 us per 2^20 pixels at d = 1, 0.75 at d = 1 and 2, 1.2 at d = 1, 2 and 4;
+// the row kernels take 10-17 us and about 0.05 + 0.13 per offset.  Measured on
+// MI355X, N = 16, vote kernel in us, against strips or slabs: 300^2 8.9 / 19.0
+// (four offsets at d = 1), 12.0 / 15.7 (two of d = 1 and 2), 14.4 / 13.1 (seven
+// of d = 1, 2 and 4); 1000^2 9.4 / 19.7, 7.7 / 15.9 (one offset), 12.3 / 18.7,
+// 15.1 / 17.1; 2937 x 3015 off the 16-byte grid 12.5 / 19.2, 11.2 / 15.8,
+// 18.1 / 18.1, 24.8 / 23.5, 24.8 / 34.4 (all twelve); 4096^2 16.6 / 18.2,
+// 14.5 / 13.7, 23.2 / 14.4, 23.2 / 26.2 (all eight), 34.3 / 24.8, 34.3 / 40.0;
+// 8192^2 35.5 / 41.2, 34.1 / 22.1, 61 / 76 (eight), 95 / 137 (twelve).
+bool onehot_pays(const glcm_plan_s* p, int reach, uint64_t pixels) {
+  const Canon c = canonicalize(p->offsets, p->K);
+  uint32_t wanted = 0;
+  for (int k = 0; k < p->K; ++k) wanted |= 1u << glcm::onehot_slot(c.dx[k], c.dy[k]);
+  const int slots = __builtin_popcount(wanted);
+  const int groups = ((wanted & 0xfu) != 0) + ((wanted & 0xf0u) != 0) + ((wanted & 0xf00u) != 0);
+  if (slots >= 3 * groups) return true;
+  return pixels <= (reach == 4 ? 1u << 21 : 1u << 23) && (reach != 4 || pixels >= 1u << 18);
+}
+
+// Rows per segment for `rows` first-pixel rows (of which none has rows below
+// it in the image when `last`): h + reach a multiple of the kernel's stride, at
+// least a block of converted rows where there are as many, and long enough
+// that the (window, segment) tasks, four to a wavefront, fill `waves`
+// wavefronts at most once.  0: fewer rows than the shortest segment.
+int onehot_segment_rows(int windows, int rows, bool last, int reach, int64_t waves) {
+  const int U = glcm::onehot_stride(reach);
+  if (rows < U - reach) return last ? U - reach : 0;
+  for (int n = glcm::onehot_block_rows(reach) / U;; ++n) {
+    const int h = U * n - reach;
+    if (h > rows) return U * ((rows + reach) / U) - reach;  // one or two segments of nearly all rows
+    const int64_t tasks = (int64_t)windows * ((rows + h - 1) / h);
+    if ((tasks + 3) / 4 <= waves) return h;
+  }
 }
 
 // Image passes of the partitioned kernel worth one GLCM's pairs added into
@@ -785,12 +837,81 @@ int count_levels(glcm_plan_t p, const VoteArgs& v, int b, uint32_t* out, bool ac
   return GLCM_OK;
 }
 
+// Counts rows [y_begin, y_end) with the matrix-core kernel; *done = false (and
+// nothing queued) where it does not apply.  `alone`: the call's only counting
+// launch, so that one workgroup may store its counts to out.
+// Measured on MI355X, glcm_compute of an image one workgroup counts: one launch
+// instead of two.
+int count_onehot(glcm_plan_t p, const VoteArgs& v, int b, uint32_t* out, bool accumulate, bool finish, bool alone,
+                 hipStream_t stream, bool* done) {
+  *done = false;
+  const int reach = onehot_reach(p->offsets, p->K, p->N);
+  if (reach == 0 || !onehot_pays(p, reach, (uint64_t)v.W * (uint64_t)(v.y_end - v.y_begin))) return GLCM_OK;
+  const int rows = v.y_end - v.y_begin, windows = glcm::onehot_windows(v.W, reach);
+  const int kWaves = glcm::onehot_threads(reach) / 64, per_cu = glcm::onehot_per_cu(reach);
+  const int64_t waves = (int64_t)std::max(1, p->num_cus) * per_cu * kWaves;
+  // few enough rows of windows: one workgroup, which needs no merge
+  const bool single = alone && finish && !accumulate && (int64_t)windows * rows <= 4 * kWaves * 64;
+  const int h = onehot_segment_rows(windows, rows, v.y_end == v.H, reach, single ? kWaves : waves);
+  if (h == 0) return GLCM_OK;
+  const int64_t tasks = (int64_t)windows * ((rows + h - 1) / h), units = (tasks + 3) / 4;
+  const int groups = single ? 1 : (int)std::min<int64_t>((units + kWaves - 1) / kWaves, waves / kWaves);
+  // a wavefront's fp32 sums are exact below 2^24 pairs
+  if ((units + (int64_t)groups * kWaves - 1) / ((int64_t)groups * kWaves) * (4 * glcm::kOnehotWindow) * (int64_t)h >= (1 << 24))
+    return GLCM_OK;
+  if (tasks > (1 << 30)) return GLCM_OK;
+  const Canon c = canonicalize(p->offsets, p->K);
+  glcm::OnehotArgs a;
+  std::memset(&a, 0, sizeof(a));
+  a.img = v.img;
+  a.stride = v.stride;
+  a.W = v.W;
+  a.H = v.H;
+  a.y_begin = v.y_begin;
+  a.y_end = v.y_end;
+  a.q = v.q;
+  a.qfast = v.qfast;
+  a.qfast_shift = v.qfast_shift;
+  a.qfast_mask = v.qfast_mask;
+  a.K = p->K;
+  int dist = 0;
+  for (int k = 0; k < p->K; ++k) {
+    a.slot[k] = (int8_t)glcm::onehot_slot(c.dx[k], c.dy[k]);
+    dist |= 1 << (a.slot[k] / 4);
+  }
+  a.tmask = c.tmask;
+  a.windows = windows;
+  a.h = h;
+  a.tasks = (int)tasks;
+  a.words_total = v.words_total;
+  a.xbuf = single ? nullptr : p->xbuf;
+  a.out = out;
+  a.accumulate = 0;
+  glcm::LaunchTiming tm;
+  if (p->flags & GLCM_FLAG_TIMING) {
+    GLCM_TRY(hipEventCreate(&tm.start));
+    GLCM_TRY(hipEventCreate(&tm.stop));
+    p->timing.emplace_back(tm.start, tm.stop);
+  }
+  *done = true;
+  hipError_t e = glcm::launch_vote_onehot(a, b, dist, groups, stream, tm);
+  if (e == hipSuccess && finish && !single)
+    e = glcm::launch_finish(p->xbuf, out, v.words_total, p->xslots, accumulate, stream);
+  if (e != hipSuccess) {
+    (void)glcm::launch_zero(p->xbuf, (uint64_t)p->xslots * v.words_total, stream);
+    return hip_status(e);
+  }
+  return GLCM_OK;
+}
+
 // Queues the counting of first-pixel rows [y_begin, y_end) of a device image
 // whose rows [0, H) are all resident, writing (or adding into) out.
 // finish = false leaves the counts in the per-XCD accumulators (host tiles);
-// the last call then finishes with accumulate = false.
+// the last call then finishes with accumulate = false.  `alone`: no other call
+// adds to the same result.
 int count_device(glcm_plan_t p, const void* img, int W, int H, int64_t stride, int y_begin, int y_end,
-                 uint32_t lo, uint32_t hi, uint32_t* out, bool accumulate, bool finish, hipStream_t stream) {
+                 uint32_t lo, uint32_t hi, uint32_t* out, bool accumulate, bool finish, hipStream_t stream,
+                 bool alone = false) {
   const glcm_tuning_t& t = p->tuning;
   const int b = dtype_bytes(p->dtype);
   const uint32_t NN = (uint32_t)p->N * (uint32_t)p->N;
@@ -815,6 +936,14 @@ int count_device(glcm_plan_t p, const void* img, int W, int H, int64_t stride, i
   a.out = out;
 
   int path = t.path;
+  constexpr uint32_t kForced = GLCM_FLAG_FORCE_GENERIC | GLCM_FLAG_FORCE_PARTITIONED | GLCM_FLAG_FORCE_GLOBAL |
+                               GLCM_FLAG_FORCE_SLABS | GLCM_FLAG_FORCE_L2 | GLCM_FLAG_FORCE_BLOCKS;
+  if ((path == kPathRows || path == kPathStrips) && !p->user_tuned && !(p->flags & kForced) && t.merge == 0 &&
+      p->xbuf && y_end > y_begin) {
+    bool done = false;
+    const int rc = count_onehot(p, a, b, out, accumulate, finish, alone, stream, &done);
+    if (done || rc != GLCM_OK) return rc;
+  }
   const Canon c = canonicalize(p->offsets, p->K);
   // the block kernel merges into the per-XCD slices only
   if (path == kPathBlocks && (t.merge != 0 || !p->xbuf)) path = kPathStrips;
@@ -1429,6 +1558,7 @@ GLCM_API int glcm_plan_tuning(glcm_plan_t plan, glcm_tuning_t* tuning, int set) 
     }
     if (n.merge != 0 && n.merge != 1) return GLCM_EINVAL;
     if (n.merge == 0 && !plan->xbuf && t.path != kPathGlobal) return GLCM_EINVAL;
+    const glcm_tuning_t before = t;
     t.counter_bits = bits;
     t.merge = n.merge;
     t.replicas = n.replicas;
@@ -1441,7 +1571,11 @@ GLCM_API int glcm_plan_tuning(glcm_plan_t plan, glcm_tuning_t* tuning, int set) 
     }
     t.path = new_path;
     t.tile_rows = n.tile_rows;
-    plan->user_tuned = true;
+    // (the upload tile height alone names no kernel)
+    if (before.replicas != t.replicas || before.wg_size != t.wg_size || before.rows_per_wave != t.rows_per_wave ||
+        before.counter_bits != t.counter_bits || before.merge != t.merge || before.path != t.path ||
+        before.partitions != t.partitions)
+      plan->user_tuned = true;
   }
   *tuning = plan->tuning;
   return GLCM_OK;
@@ -1567,8 +1701,11 @@ GLCM_API int glcm_plan_autotune(glcm_plan_t plan, const void* img, int W, int H,
   if (he == hipSuccess) he = hipEventCreate(&e1);
   if (he != hipSuccess) rc = hip_status(he);
   if (rc == GLCM_OK) rc = order_after_previous(plan, stream);
+  const bool was_tuned = plan->user_tuned;
+  size_t best_c = 0;
   for (size_t c = 0; c < cand.size() && rc == GLCM_OK; ++c) {
     plan->tuning = cand[c];
+    plan->user_tuned = c == 0 ? was_tuned : true;  // the first is what the plan does now, whatever kernel that is
     for (int i = 0; i < 2 && rc == GLCM_OK; ++i)
       rc = count_device(plan, img, W, H, stride, 0, H, lo, hi, out, false, true, stream);
     if (rc != GLCM_OK) break;
@@ -1587,6 +1724,7 @@ GLCM_API int glcm_plan_autotune(glcm_plan_t plan, const void* img, int W, int H,
     if (c == 0 || ms < 0.97f * best) {
       best = ms;
       best_t = cand[c];
+      best_c = c;
     }
   }
   if (rc == GLCM_OK) rc = record_done(plan, stream);
@@ -1595,7 +1733,7 @@ GLCM_API int glcm_plan_autotune(glcm_plan_t plan, const void* img, int W, int H,
   if (e1) (void)hipEventDestroy(e1);
   (void)hipFree(out);
   plan->tuning = rc == GLCM_OK ? best_t : start;
-  if (rc == GLCM_OK) plan->user_tuned = true;
+  plan->user_tuned = rc == GLCM_OK && best_c != 0 ? true : was_tuned;
   if (chosen) *chosen = plan->tuning;
   return rc;
 }
@@ -1697,7 +1835,7 @@ int compute_in_workspace(uint32_t* slices, size_t slice_words, const void* img, 
   // the slices start at zero whatever an earlier call left (a fill kernel:
   // the call stays capturable in a graph)
   GLCM_TRY(launch_zero(slices, (uint64_t)kXcdSlots * words, stream));
-  return count_device(&p, img, W, H, stride, 0, H, lo, hi, out, false, true, stream);
+  return count_device(&p, img, W, H, stride, 0, H, lo, hi, out, false, true, stream, true);
 }
 
 }  // namespace glcm
@@ -1740,7 +1878,7 @@ GLCM_API int glcm_compute(glcm_plan_t plan, const void* img, int W, int H, int64
   rc = order_after_previous(plan, stream);
   if (rc != GLCM_OK) return rc;
   if (kind == 2) {
-    rc = count_device(plan, img, W, H, stride, 0, H, lo, hi, out, false, true, stream);
+    rc = count_device(plan, img, W, H, stride, 0, H, lo, hi, out, false, true, stream, true);
   } else {
     rc = count_host(plan, img, kind == 1, W, H, stride, lo, hi, out, stream);
   }

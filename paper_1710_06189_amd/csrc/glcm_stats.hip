@@ -26,13 +26,6 @@ constexpr int kStatsThreads = 256;
 constexpr int kStatsWaves = kStatsThreads / 64;
 constexpr int kWaveMaxN = 32;
 
-// Orders a wavefront's LDS writes before its lanes read each other's words.
-__device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // c / T correctly rounded, with r = 1 / T correctly rounded (Markstein 1990:
 // each step adds the exactly known remainder times the reciprocal; the first
 // leaves a faithful quotient, the second the nearest).  c and T are integers
@@ -113,13 +106,13 @@ __global__ __launch_bounds__(kStatsThreads) void k_symmetrize_wave(StatsArgs a) 
   for (int k = (int)blockIdx.x * kStatsWaves + (int)(threadIdx.x >> 6); k < a.K; k += nwaves) {
     uint32_t c[kWords<L>];
     load_matrix<L, VEC>(c, a.in + (size_t)k * NN, NN, lane);
-    wave_lds_sync();  // the previous matrix's reads of M are done
+    wave_sync_lds();  // the previous matrix's reads of M are done
 #pragma unroll
     for (int v = 0; v < kWords<L>; ++v) {
       const uint32_t r = word_of<VEC>(lane, v), i = divide(r, a.nmagic, a.nshift);
       if (r < NN) M[i * p + (r - i * N)] = c[v];
     }
-    wave_lds_sync();
+    wave_sync_lds();
 #pragma unroll
     for (int v = 0; v < kWords<L>; ++v) {
       const uint32_t r = word_of<VEC>(lane, v), i = divide(r, a.nmagic, a.nshift);
@@ -401,7 +394,7 @@ __global__ __launch_bounds__(kStatsThreads, L == 16 ? 4 : 3) void k_haralick_wav
   for (int k = (int)blockIdx.x * kStatsWaves + (int)(threadIdx.x >> 6); k < a.K; k += nwaves) {
     uint32_t c[kWords<L>];
     load_matrix<L, VEC>(c, a.in + (size_t)k * NN, NN, lane);
-    wave_lds_sync();  // the previous matrix's reads of M are done
+    wave_sync_lds();  // the previous matrix's reads of M are done
     double T = 0.0;
 #pragma unroll
     for (int v = 0; v < kWords<L>; ++v) {
@@ -416,7 +409,7 @@ __global__ __launch_bounds__(kStatsThreads, L == 16 ? 4 : 3) void k_haralick_wav
       if (lane == 0) st->asm_ = -1.0;  // empty: zeros
     } else {
       const double inv = 1.0 / T;
-      wave_lds_sync();
+      wave_sync_lds();
 #pragma unroll
       for (int pass = 0; pass < (L == 16 ? 1 : 2); ++pass) {
         // 0 rows, 1 columns, 2 |i - j|, 3 i + j
@@ -490,7 +483,7 @@ __global__ __launch_bounds__(kStatsThreads, L == 16 ? 4 : 3) void k_haralick_wav
       }
     }
     if (++held == kPark || k + nwaves >= a.K) {
-      wave_lds_sync();
+      wave_sync_lds();
       if (lane < held) {
         float* f = a.out_f + (size_t)(k_first + lane * nwaves) * kHaralickStats;
         const Moments s = park[lane];
@@ -500,7 +493,7 @@ __global__ __launch_bounds__(kStatsThreads, L == 16 ? 4 : 3) void k_haralick_wav
           haralick_store(s, f);
         }
       }
-      wave_lds_sync();
+      wave_sync_lds();
       held = 0;
     }
   }

@@ -66,6 +66,14 @@ __device__ __forceinline__ double sum_xor32(double v) { return v + __shfl_xor(v,
 __device__ __forceinline__ uint64_t sum_xor16(uint64_t v) { return v + (uint64_t)__shfl_xor((unsigned long long)v, 16); }
 __device__ __forceinline__ uint64_t sum_xor32(uint64_t v) { return v + (uint64_t)__shfl_xor((unsigned long long)v, 32); }
 
+// Orders a wavefront's LDS writes before its lanes read each other's words
+// (and its reads before later writes).
+__device__ __forceinline__ void wave_sync_lds() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Lane Q of each group of four, on all four (quad_perm:[Q,Q,Q,Q]).
 template <int Q>
 __device__ __forceinline__ double quad_bcast(double v) {
