@@ -228,7 +228,7 @@ struct glcm_plan_s {
   // batch descriptors: pinned staging and its device copy
   void* batch_pin = nullptr;
   void* batch_dev = nullptr;
-  size_t batch_cap = 0;
+  size_t batch_cap = 0, batch_pin_cap = 0;
   hipEvent_t batch_uploaded = nullptr;
   bool batch_pending = false;
 
@@ -840,8 +840,8 @@ int count_levels(glcm_plan_t p, const VoteArgs& v, int b, uint32_t* out, bool ac
 // Counts rows [y_begin, y_end) with the matrix-core kernel; *done = false (and
 // nothing queued) where it does not apply.  `alone`: the call's only counting
 // launch, so that one workgroup may store its counts to out.
-// Measured on MI355X, glcm_compute of an image one workgroup counts: one launch
-// instead of two.
+// Measured on MI355X, 64 x 64 at N = 16, d = 1: 19.5 us of kernels in two
+// launches (count, merge), 5.0 in one.
 int count_onehot(glcm_plan_t p, const VoteArgs& v, int b, uint32_t* out, bool accumulate, bool finish, bool alone,
                  hipStream_t stream, bool* done) {
   *done = false;
@@ -1891,10 +1891,14 @@ namespace {
 // What a batch launch needs besides lo, hi and the output pointers.
 struct BatchLayout {
   int D = 0, smd = 1, b = 1, wg = glcm::kBatchThreads;
+  bool onehot = false;  // the matrix-core kernel
   size_t lds_bytes = 0;
   int groups = 0;  // persistent workgroups: as many as the CUs hold at once
   glcm::BatchArgs args{};  // offsets, codes and layout; quantizer and outputs filled per launch
 };
+
+constexpr int kBatchMinBandRows = 8;  // rows of a band of a split image
+constexpr int kOnehotMaxW = 1 << 19;    // widest image of a batch on the matrix cores
 
 // Checks a batch request against the plan and picks its LDS layout.
 // The default LDS layout of the batch kernel: the most dwords per bin (16, 8
@@ -1911,8 +1915,10 @@ int batch_default_copies(const glcm_plan_s* plan) {
 int batch_layout(glcm_plan_t plan, const glcm_tile_t* tiles, int T, BatchLayout* L) {
   if (!plan || !tiles || T < 1 || T > (1 << 20)) return GLCM_EINVAL;
   const int b = dtype_bytes(plan->dtype);
+  int widest = 0;
   for (int t = 0; t < T; ++t) {
     const glcm_tile_t& e = tiles[t];
+    widest = std::max(widest, e.W);
     if (!e.img || e.W < 1 || e.H < 1 || e.W > plan->max_W || e.H > plan->max_H || e.stride < e.W) return GLCM_EINVAL;
     if ((uint64_t)e.W * (uint64_t)e.H > 0xffffffffull || ((uintptr_t)e.img % (uintptr_t)b)) return GLCM_EINVAL;
   }
@@ -1929,6 +1935,11 @@ int batch_layout(glcm_plan_t plan, const glcm_tile_t* tiles, int T, BatchLayout*
   const int per_cu = std::max(1, std::min((int)(lds_cu / lds_bytes), 32 / (L->wg / 64)));
   L->groups = per_cu * std::max(1, plan->num_cus);
   L->smd = std::max(c.maxdy, c.maxadx) <= 1 ? 1 : 2;
+  // up to 16 levels along the four directions: the matrix cores, unless a
+  // layout of the LDS kernel was asked for (or kept by the autotuner)
+  L->onehot = !plan->batch_D && !plan->batch_min_rows && !plan->batch_wg && widest <= kOnehotMaxW &&
+              onehot_reach(plan->offsets, plan->K, plan->N) != 0;
+  if (L->onehot) L->groups = glcm::kBatchOnehotPerCu * std::max(1, plan->num_cus);
   glcm::BatchArgs& a = L->args;
   std::memset(&a, 0, sizeof(a));
   a.K = plan->K;
@@ -1936,6 +1947,7 @@ int batch_layout(glcm_plan_t plan, const glcm_tile_t* tiles, int T, BatchLayout*
     a.dx[k] = plan->offsets[k].dx;
     a.dy[k] = plan->offsets[k].dy;
     a.vcode[k] = c.dy[k] * (2 * L->smd + 1) + c.dx[k] + L->smd;
+    a.slot[k] = glcm::onehot_slot(c.dx[k], c.dy[k]);
   }
   a.tmask = c.tmask;
   a.pitch = (uint32_t)plan->N + 1u;
@@ -1955,16 +1967,22 @@ std::pair<uintptr_t, uintptr_t> tile_extent(const glcm_tile_t& e, int b) {
 
 // Every tile must lie inside one device allocation of the current device (the
 // kernel reads it with plain loads; a host pointer would fault the GPU).
-// Allocations are looked up once each (hipMemGetAddressRange), then tiles
-// inside a known allocation cost one map lookup.
+// Allocations are looked up once a call each (hipMemGetAddressRange); a tile
+// is compared with the one the tile before it lay in first, then with the
+// others (a sorted list).
 int check_tile_memory(const glcm_tile_t* tiles, int T, int b) {
   int cur = 0;
   GLCM_TRY(hipGetDevice(&cur));
-  std::map<uintptr_t, uintptr_t> known;  // allocation base -> end
+  std::vector<std::pair<uintptr_t, uintptr_t>> known;  // allocation base, end; sorted
+  std::pair<uintptr_t, uintptr_t> last{1, 0};
   for (int t = 0; t < T; ++t) {
     const auto x = tile_extent(tiles[t], b);
-    auto it = known.upper_bound(x.first);
-    if (it != known.begin() && x.first >= std::prev(it)->first && x.second <= std::prev(it)->second) continue;
+    if (x.first >= last.first && x.second <= last.second) continue;
+    auto it = std::upper_bound(known.begin(), known.end(), std::make_pair(x.first, UINTPTR_MAX));
+    if (it != known.begin() && x.second <= std::prev(it)->second) {
+      last = *std::prev(it);
+      continue;
+    }
     int dev = -1;
     if (pointer_kind(tiles[t].img, &dev) != 2 || dev != cur) return GLCM_EINVAL;
     hipDeviceptr_t base = nullptr;
@@ -1975,35 +1993,45 @@ int check_tile_memory(const glcm_tile_t* tiles, int T, int b) {
     }
     const uintptr_t a0 = (uintptr_t)base, a1 = a0 + size;
     if (x.first < a0 || x.second > a1) return GLCM_EINVAL;
-    known[a0] = a1;
+    last = {a0, a1};
+    known.insert(it, last);
   }
   return GLCM_OK;
 }
 
 // No tile may overlap [o0, o1) (an output the kernel writes while it reads
 // the tiles).
-bool tiles_clear_of(const std::vector<std::pair<uintptr_t, uintptr_t>>& ext, uintptr_t o0, uintptr_t o1) {
-  for (const auto& x : ext)
-    if (x.first < o1 && o0 < x.second) return false;
-  return true;
+extern "C++" {
+
+template <class Extent>
+bool tiles_clear_of(Extent at, int T, uintptr_t o0, uintptr_t o1) {
+  bool clear = true;
+  for (int t = 0; t < T; ++t) {
+    const auto x = at(t);
+    clear &= !(x.first < o1 && o0 < x.second);
+  }
+  return clear;
 }
 
 // Output pointers of a batch launch: device memory of the current device,
 // clear of every tile.
-int check_batch_outputs(const std::vector<std::pair<uintptr_t, uintptr_t>>& ext, int T, int K, int N,
-                        const uint32_t* out, const float* features) {
+// (at(t): byte range of tile t)
+template <class Extent>
+int check_batch_outputs(Extent at, int T, int K, int N, const uint32_t* out, const float* features) {
   int cur = 0, dev = -1;
   GLCM_TRY(hipGetDevice(&cur));
   if (pointer_kind(out, &dev) != 2 || dev != cur) return GLCM_EINVAL;
   if (features && (pointer_kind(features, &dev) != 2 || dev != cur)) return GLCM_EINVAL;
   const uintptr_t o0 = (uintptr_t)out, o1 = o0 + (uintptr_t)T * (uintptr_t)K * (uintptr_t)N * (uintptr_t)N * 4u;
-  if (!tiles_clear_of(ext, o0, o1)) return GLCM_EINVAL;
+  if (!tiles_clear_of(at, T, o0, o1)) return GLCM_EINVAL;
   if (features) {
     const uintptr_t f0 = (uintptr_t)features, f1 = f0 + (uintptr_t)T * (uintptr_t)K * 5u * 4u;
-    if (!tiles_clear_of(ext, f0, f1) || (f0 < o1 && o0 < f1)) return GLCM_EINVAL;
+    if (!tiles_clear_of(at, T, f0, f1) || (f0 < o1 && o0 < f1)) return GLCM_EINVAL;
   }
   return GLCM_OK;
 }
+
+}  // extern "C++"
 
 std::vector<std::pair<uintptr_t, uintptr_t>> tile_extents(const glcm_tile_t* tiles, int T, int b) {
   std::vector<std::pair<uintptr_t, uintptr_t>> ext((size_t)T);
@@ -2022,34 +2050,109 @@ std::vector<std::pair<uintptr_t, uintptr_t>> tile_extents(const glcm_tile_t* til
 // batch 291 us against 245 us whole, though the largest image alone fell
 // from 114 to 44 us.
 constexpr uint64_t kBatchItemPixels = 1u << 18, kBatchSplitPixels = 1u << 20;
-constexpr int kBatchMinBandRows = 8;
+// The matrix-core kernel's items cost less to set up: a band is a workgroup's
+// fair share of the batch (of kOnehotShares), though not below
+// kOnehotMinPixels, and an image of more than two is split; at most
+// kOnehotMaxPixels, so that a wavefront's fp32 sums stay exact (below 2^24
+// pairs an item; kOnehotMaxW bounds the bands of the least rows).  In a batch
+// of more items than shares, those below kOnehotWavePixels are counted by one
+// wavefront each.  Measured on MI355X (d = 1, N = 16, with the statistics):
+// 4096 images of 32-512 px 125 us (bands of a fixed 2^16 pixels 140 us, no
+// bands 125 us); one of 512 x 512 32 us (no bands 62 us); 4096 of 64 x 64 51 us
+// by wavefronts, 75 us by workgroups; 4096 of 32-512 px with less than 2^16
+// pixels 99 us, 114 us with wavefronts up to 2^14 pixels.
+constexpr uint64_t kOnehotShares = 1024, kOnehotMinPixels = 1u << 16, kOnehotMaxPixels = 1u << 22;
+constexpr uint64_t kOnehotWavePixels = 1u << 13;
+static_assert((2 * kBatchMinBandRows - 1) * (uint64_t)kOnehotMaxW < (1u << 24) &&
+                  2 * kOnehotMaxPixels + kOnehotMaxW < (1u << 24),
+              "an item's pairs are counted exactly");
 
 constexpr size_t kBatchDescOff = 256;
 
+// Items go by descending size class (32 to an octave of pixels), a counting
+// sort: the order only has to keep the large ones ahead.
 struct BatchItems {
-  std::vector<glcm::BatchTile> items;
-  std::vector<glcm::BatchFin> fins;
+  int nitems = 0, nfins = 0;
   int slots = 0;   // band rows of partial counts
+  int big = 0;     // matrix-core kernel: items of at least kOnehotWavePixels
   int tables = 0;  // entries of the per-image destination tables (0: one contiguous output)
-  // device layout: the item counter (at offset 0 whatever the batch, so a
-  // buffer reused for another batch keeps it zero), the items from offset
+  uint64_t piece = kBatchItemPixels, split = kBatchSplitPixels;  // pixels of a band, of the largest whole image
+  static constexpr int kClasses = 33 * 32;
+  int first[kClasses];  // position of the next item of a class
+  // device layout: the item counters (at offset 0 whatever the batch, so a
+  // buffer reused for another batch keeps them zero), the items from offset
   // kBatchDescOff, the fins, the destination tables (counts, then
   // statistics), then the partial rows (256-byte aligned)
-  size_t fins_off() const { return kBatchDescOff + items.size() * sizeof(glcm::BatchTile); }
-  size_t tables_off() const { return (fins_off() + fins.size() * sizeof(glcm::BatchFin) + 7u) & ~(size_t)7u; }
+  size_t fins_off() const { return kBatchDescOff + (size_t)nitems * sizeof(glcm::BatchTile); }
+  size_t tables_off() const { return (fins_off() + (size_t)nfins * sizeof(glcm::BatchFin) + 7u) & ~(size_t)7u; }
   size_t tables_end() const { return tables_off() + 2u * (size_t)tables * sizeof(void*); }
   size_t partials_off() const { return (tables_end() + 255u) & ~(size_t)255u; }
   size_t desc_bytes() const { return tables_end() - kBatchDescOff; }
   size_t dev_bytes(int K, int N) const { return partials_off() + (size_t)slots * K * N * N * 4u; }
+
+  // class of an item of n pixels, the largest first
+  static int size_class(uint64_t n) {
+    const uint32_t v = (uint32_t)n;  // an image has at most 2^32 - 1 pixels
+    const int e = 31 - __builtin_clz(v | 1u);
+    const uint32_t m = e >= 5 ? (v >> (e - 5)) & 31u : (v << (5 - e)) & 31u;
+    return kClasses - 1 - (e * 32 + (int)m);
+  }
+  // bands of a tile: rows each and how many (1: whole)
+  void bands(const glcm_tile_t& e, int* rows, int* parts) const {
+    const uint64_t area = (uint64_t)e.W * (uint64_t)e.H;
+    *rows = e.H;
+    *parts = 1;
+    if (area <= split) return;
+    const int n = (int)std::min<uint64_t>((area + piece - 1) / piece, (uint64_t)std::max(1, e.H / kBatchMinBandRows));
+    *rows = (e.H + n - 1) / n;
+    *parts = (e.H + *rows - 1) / *rows;
+  }
 };
 
-void batch_items(const glcm_tile_t* tiles, int T, int b, BatchItems* it) {
-  it->items.clear();
-  it->fins.clear();
-  it->slots = 0;
-  it->tables = 0;
+// Counts the items, their classes' positions and the bands' rows.
+void batch_items(const glcm_tile_t* tiles, int T, bool onehot, BatchItems* it) {
+  it->nitems = it->nfins = it->slots = it->big = it->tables = 0;
+  if (onehot) {
+    uint64_t total = 0;  // (below 2^52)
+    for (int t = 0; t < T; ++t) total += (uint64_t)tiles[t].W * (uint64_t)tiles[t].H;
+    it->piece = std::min(std::max(total / kOnehotShares, kOnehotMinPixels), kOnehotMaxPixels);
+    it->split = 2 * it->piece;
+  }
+  int count[BatchItems::kClasses] = {};
   for (int t = 0; t < T; ++t) {
     const glcm_tile_t& e = tiles[t];
+    int rows = 0, parts = 0;
+    it->bands(e, &rows, &parts);
+    if (parts > 1) {
+      const int tail = e.H - (parts - 1) * rows;
+      count[BatchItems::size_class((uint64_t)e.W * (uint64_t)rows)] += parts - 1;
+      count[BatchItems::size_class((uint64_t)e.W * (uint64_t)tail)] += 1;
+      it->nfins += 1;
+      it->slots += parts;
+    } else {
+      count[BatchItems::size_class((uint64_t)e.W * (uint64_t)e.H)] += 1;
+    }
+    it->nitems += parts;
+  }
+  const int small = BatchItems::size_class(kOnehotWavePixels);  // (a class of its own first pixel count)
+  for (int c = 0, n = 0; c < BatchItems::kClasses; ++c) {
+    it->first[c] = n;
+    n += count[c];
+    if (c == small) it->big = n;
+  }
+  if (it->nitems <= (int)kOnehotShares) it->big = it->nitems;
+}
+
+// Writes the descriptors (items, then fins: desc_bytes() bytes less the
+// tables, uploaded to offset kBatchDescOff) to `host`.
+void batch_descriptors(BatchItems* it, const glcm_tile_t* tiles, int T, int b, void* host) {
+  glcm::BatchTile* items = (glcm::BatchTile*)host;
+  glcm::BatchFin* fins = (glcm::BatchFin*)((char*)host + (size_t)it->nitems * sizeof(glcm::BatchTile));
+  int fin = 0, slot = 0;
+  for (int t = 0; t < T; ++t) {
+    const glcm_tile_t& e = tiles[t];
+    int rows = 0, parts = 0;
+    it->bands(e, &rows, &parts);
     glcm::BatchTile d{};
     d.img = e.img;
     d.stride = e.stride;
@@ -2057,45 +2160,20 @@ void batch_items(const glcm_tile_t* tiles, int T, int b, BatchItems* it) {
     d.H = e.H;
     d.index = t;
     d.unaligned = tile_aligned(e, b) ? 0 : 1;
-    const uint64_t area = (uint64_t)e.W * (uint64_t)e.H;
-    int parts = 1;
-    if (area > kBatchSplitPixels)
-      parts = (int)std::min<uint64_t>((area + kBatchItemPixels - 1) / kBatchItemPixels,
-                                      (uint64_t)std::max(1, e.H / kBatchMinBandRows));
-    if (parts <= 1) {
-      d.y0 = 0;
-      d.y1 = e.H;
-      d.slot = -1;
-      it->items.push_back(d);
-      continue;
-    }
-    const int rp = (e.H + parts - 1) / parts;
-    parts = (e.H + rp - 1) / rp;
-    it->fins.push_back(glcm::BatchFin{t, it->slots, parts, 0});
+    d.slot = -1;
+    if (parts > 1) fins[fin++] = glcm::BatchFin{t, slot, parts, 0};
     for (int p = 0; p < parts; ++p) {
-      d.y0 = p * rp;
-      d.y1 = std::min(e.H, (p + 1) * rp);
-      d.slot = it->slots + p;
-      it->items.push_back(d);
+      d.y0 = p * rows;
+      d.y1 = std::min(e.H, (p + 1) * rows);
+      if (parts > 1) d.slot = slot++;
+      items[it->first[BatchItems::size_class((uint64_t)e.W * (uint64_t)(d.y1 - d.y0))]++] = d;
     }
-    it->slots += parts;
   }
-  std::stable_sort(it->items.begin(), it->items.end(), [](const glcm::BatchTile& x, const glcm::BatchTile& y) {
-    return (uint64_t)x.W * (uint64_t)(x.y1 - x.y0) > (uint64_t)y.W * (uint64_t)(y.y1 - y.y0);
-  });
-}
-
-// Copies the descriptors (items, then fins: desc_bytes() bytes, uploaded to
-// offset kBatchDescOff) to `host`.
-void batch_descriptors(const BatchItems& it, void* host) {
-  const size_t ib = it.items.size() * sizeof(glcm::BatchTile);
-  std::memcpy(host, it.items.data(), ib);
-  if (!it.fins.empty()) std::memcpy((char*)host + ib, it.fins.data(), it.fins.size() * sizeof(glcm::BatchFin));
 }
 
 // Queues the fused batch kernel (and the sum of the split images' bands).
-// The item counter (the buffer's first word) must be zero.
-int batch_launch(const BatchLayout& L, int nitems, int nfins, size_t fins_off, size_t partials_off,
+// The item counters (the buffer's first two words) must be zero.
+int batch_launch(const BatchLayout& L, int nitems, int nbig, int nfins, size_t fins_off, size_t partials_off,
                  const void* desc_dev, uint32_t N, uint32_t lo, uint32_t hi, uint32_t* out, float* features,
                  hipStream_t stream, uint32_t* const* outs = nullptr, float* const* feats = nullptr) {
   glcm::BatchArgs a = L.args;
@@ -2106,12 +2184,18 @@ int batch_launch(const BatchLayout& L, int nitems, int nfins, size_t fins_off, s
   a.partials = (uint32_t*)((char*)const_cast<void*>(desc_dev) + partials_off);
   a.counter = (uint32_t*)const_cast<void*>(desc_dev);
   a.nitems = nitems;
+  a.nbig = nbig;
   a.nfins = nfins;
   a.out = out;
   a.feat = features;
   a.outs = outs;
   a.feats = feats;
-  GLCM_TRY(glcm::launch_batch(a, std::min(nitems, L.groups), L.b, L.smd, L.D, L.wg, L.lds_bytes, stream));
+  if (L.onehot)
+    GLCM_TRY(glcm::launch_batch_onehot(
+        a, std::min(nbig + (nitems - nbig + 3) / 4, L.groups), L.b, L.smd,
+        stream));
+  else
+    GLCM_TRY(glcm::launch_batch(a, std::min(nitems, L.groups), L.b, L.smd, L.D, L.wg, L.lds_bytes, stream));
   GLCM_TRY(glcm::launch_batch_fin(a, nfins, stream));
   return GLCM_OK;
 }
@@ -2132,30 +2216,38 @@ int batch_compute_common(glcm_plan_t plan, const glcm_tile_t* tiles, int T, uint
   int rc = batch_layout(plan, tiles, T, &L);
   if (rc != GLCM_OK) return rc;
   GLCM_TRY_RC(check_tile_memory(tiles, T, L.b));
-  if (!outs) GLCM_TRY_RC(check_batch_outputs(tile_extents(tiles, T, L.b), T, plan->K, plan->N, out, features));
+  if (!outs) {
+    const auto at = [&](int t) { return tile_extent(tiles[t], L.b); };
+    GLCM_TRY_RC(check_batch_outputs(at, T, plan->K, plan->N, out, features));
+  }
   GLCM_TRY_RC(order_after_previous(plan, stream));
   BatchItems it;
-  batch_items(tiles, T, L.b, &it);
+  batch_items(tiles, T, L.onehot, &it);
   if (outs) it.tables = T;
   const size_t need = it.dev_bytes(plan->K, plan->N);
   if (plan->batch_pending) GLCM_TRY(hipEventSynchronize(plan->batch_uploaded));
   plan->batch_pending = false;
-  if (need > plan->batch_cap) {
+  if (it.desc_bytes() > plan->batch_pin_cap) {
     if (plan->batch_pin) GLCM_TRY(hipHostFree(plan->batch_pin));
+    plan->batch_pin = nullptr;
+    plan->batch_pin_cap = 0;
+    GLCM_TRY(hipHostMalloc(&plan->batch_pin, it.desc_bytes(), hipHostMallocDefault));
+    plan->batch_pin_cap = it.desc_bytes();
+  }
+  if (need > plan->batch_cap) {
     if (plan->batch_dev) {
       if (plan->has_done) GLCM_TRY(hipEventSynchronize(plan->done));  // the last batch may still read it
       GLCM_TRY(hipFree(plan->batch_dev));
     }
-    plan->batch_pin = plan->batch_dev = nullptr;
+    plan->batch_dev = nullptr;
     plan->batch_cap = 0;
-    GLCM_TRY(hipHostMalloc(&plan->batch_pin, need, hipHostMallocDefault));
     GLCM_TRY(hipMalloc(&plan->batch_dev, need));
     plan->batch_cap = need;
-    // the item counter starts at zero (each batch launch leaves it zero again)
-    GLCM_TRY(glcm::launch_zero((uint32_t*)plan->batch_dev, need / 4u, stream));
+    // the item counters start at zero (each batch launch leaves them zero again)
+    GLCM_TRY(glcm::launch_zero((uint32_t*)plan->batch_dev, kBatchDescOff / 4u, stream));
   }
   if (!plan->batch_uploaded) GLCM_TRY(hipEventCreateWithFlags(&plan->batch_uploaded, hipEventDisableTiming));
-  batch_descriptors(it, plan->batch_pin);
+  batch_descriptors(&it, tiles, T, L.b, plan->batch_pin);
   uint32_t* const* outs_dev = nullptr;
   float* const* feats_dev = nullptr;
   if (outs) {
@@ -2170,7 +2262,7 @@ int batch_compute_common(glcm_plan_t plan, const glcm_tile_t* tiles, int T, uint
                            hipMemcpyHostToDevice, stream));
   GLCM_TRY(hipEventRecord(plan->batch_uploaded, stream));
   plan->batch_pending = true;
-  GLCM_TRY_RC(batch_launch(L, (int)it.items.size(), (int)it.fins.size(), it.fins_off(), it.partials_off(),
+  GLCM_TRY_RC(batch_launch(L, it.nitems, it.big, it.nfins, it.fins_off(), it.partials_off(),
                            plan->batch_dev, (uint32_t)plan->N, lo, hi, out, features, stream, outs_dev, feats_dev));
   return record_done(plan, stream);
 }
@@ -2198,7 +2290,7 @@ GLCM_API int glcm_batch_compute(glcm_plan_t plan, const glcm_tile_t* tiles, int 
 struct glcm_batch_s {
   BatchLayout layout;
   int T = 0;
-  int nitems = 0, nfins = 0;
+  int nitems = 0, nbig = 0, nfins = 0;
   size_t fins_off = 0, partials_off = 0;
   int dtype = 0;
   uint32_t N = 0;
@@ -2225,9 +2317,10 @@ GLCM_API int glcm_batch_prepare(glcm_plan_t plan, const glcm_tile_t* tiles, int 
   h->K = plan->K;
   h->extents = tile_extents(tiles, T, h->layout.b);
   BatchItems it;
-  batch_items(tiles, T, h->layout.b, &it);
-  h->nitems = (int)it.items.size();
-  h->nfins = (int)it.fins.size();
+  batch_items(tiles, T, h->layout.onehot, &it);
+  h->nitems = it.nitems;
+  h->nbig = it.big;
+  h->nfins = it.nfins;
   h->fins_off = it.fins_off();
   h->partials_off = it.partials_off();
   const size_t need = it.dev_bytes(plan->K, plan->N);
@@ -2236,7 +2329,7 @@ GLCM_API int glcm_batch_prepare(glcm_plan_t plan, const glcm_tile_t* tiles, int 
   if (e == hipSuccess) e = hipMalloc(&h->desc, need);
   if (e == hipSuccess) e = hipMemset(h->desc, 0, need);  // the item counter starts at zero
   if (e == hipSuccess) {
-    batch_descriptors(it, host.data());
+    batch_descriptors(&it, tiles, T, h->layout.b, host.data());
     e = hipMemcpy((char*)h->desc + kBatchDescOff, host.data(), host.size(), hipMemcpyHostToDevice);
   }
   if (e != hipSuccess) {
@@ -2252,9 +2345,10 @@ GLCM_API int glcm_batch_run(glcm_batch_t batch, uint32_t lo, uint32_t hi, uint32
                             void* stream_) {
   if (!batch || !out) return GLCM_EINVAL;
   if (lo > hi || hi > (batch->dtype == GLCM_U8 ? 255u : 65535u)) return GLCM_EINVAL;
-  GLCM_TRY_RC(check_batch_outputs(batch->extents, batch->T, batch->K, (int)batch->N, out, features));
+  GLCM_TRY_RC(check_batch_outputs([&](int t) { return batch->extents[(size_t)t]; }, batch->T, batch->K, (int)batch->N, out,
+                                  features));
   hipStream_t stream = (hipStream_t)stream_;
-  GLCM_TRY_RC(batch_launch(batch->layout, batch->nitems, batch->nfins, batch->fins_off, batch->partials_off,
+  GLCM_TRY_RC(batch_launch(batch->layout, batch->nitems, batch->nbig, batch->nfins, batch->fins_off, batch->partials_off,
                            batch->desc, batch->N, lo, hi, out, features, stream));
   // remember the launch for glcm_batch_destroy (a launch captured into a
   // graph is the caller's to wait for)
@@ -2395,11 +2489,16 @@ GLCM_API int glcm_batch_autotune(glcm_plan_t plan, const glcm_tile_t* tiles, int
   if (e == hipSuccess) e = hipEventCreate(&e1);
   if (e != hipSuccess) rc = hip_status(e);
   const int rows_grid[] = {4, 8, 16, 32};
-  for (int wg = 256; rc == GLCM_OK && wg <= 512; wg *= 2)
-  for (int D = 4; rc == GLCM_OK && D <= 16; D *= 2) {
+  bool timed = false;
+  // the default (D = 0, rows = 0, wg = 0: the matrix-core kernel where it
+  // applies) first, then the layouts of the LDS kernel
+  for (int wg = 0; rc == GLCM_OK && wg <= 512; wg = wg ? wg * 2 : 256)
+  for (int D = wg ? 4 : 0; rc == GLCM_OK && D <= 16; D = D ? D * 2 : 32) {
     const size_t lds_cu = (size_t)plan->lds_budget_words * 4u + 1024u;
-    if (glcm::batch_lds_bytes(plan->N, plan->K, D) > lds_cu - 1024u) continue;
-    for (int rows : rows_grid) {
+    if (D && glcm::batch_lds_bytes(plan->N, plan->K, D) > lds_cu - 1024u) continue;
+    for (int row : rows_grid) {
+      if (!D && row != rows_grid[0]) continue;
+      const int rows = D ? row : 0;
       {
         std::lock_guard<std::mutex> lk(plan->mu);
         plan->batch_D = D;
@@ -2421,7 +2520,8 @@ GLCM_API int glcm_batch_autotune(glcm_plan_t plan, const glcm_tile_t* tiles, int
         (void)glcm_batch_destroy(pb);
       }
       if (rc != GLCM_OK) break;
-      if (best_D == 0 || ms < best) {
+      if (!timed || ms < best) {
+        timed = true;
         best = ms;
         best_D = D;
         best_rows = rows;
@@ -2442,11 +2542,7 @@ GLCM_API int glcm_batch_autotune(glcm_plan_t plan, const glcm_tile_t* tiles, int
   if (out) (void)hipFree(out);
   if (feat) (void)hipFree(feat);
   if (rc != GLCM_OK) return rc;
-  if (chosen) {
-    chosen->replicas = best_D;
-    chosen->min_rows = best_rows;
-    chosen->wg_size = best_wg;
-  }
+  if (chosen) return glcm_batch_tuning(plan, chosen, 0);
   return GLCM_OK;
 }
 

@@ -142,8 +142,94 @@ __device__ __forceinline__ void glcm_features_wg(const uint32_t* P, uint32_t N, 
   }
 }
 
-// By one wavefront that plays all of features_waves(N), with no LDS and no
-// barrier.  Every lane must call it; lane 0 writes o.
+// N <= 16, by one wavefront: each group of 16 lanes keeps a column a lane.
+// wide: the GLCM at P, a fourth of the rows per group; else up to four GLCMs,
+// P's and the ones that follow (count in all), a group each.  o: the statistics,
+// likewise.  The sums of four rows are added in the same order either way, so
+// both give the same bits.  Every lane must call it.
+constexpr int kFeatures16 = 16;
+__device__ __forceinline__ void glcm_features_16(const uint32_t* P, uint32_t N, int count, bool wide, float* o) {
+  constexpr uint32_t U = kFeatures16 / 4;  // rows of a fourth
+  const uint32_t lane = threadIdx.x & 63u, q = lane >> 4, j = lane & 15u;
+  const uint32_t mine = wide ? 0u : q;  // this lane's GLCM
+  const bool live = (int)mine < count && j < N;
+  const uint32_t begin = wide ? U * q : 0u, end = wide ? begin + U : (N + U - 1u) / U * U;
+  P += mine * N * N;
+  unsigned long long T = 0;
+  for (uint32_t i = begin; i < end; i += U) {
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u) T += live && i + u < N ? P[(i + u) * N + j] : 0u;
+  }
+  if (wide) T = sum_xor32(sum_xor16((uint64_t)T));
+  T = row16_sum(T);
+  const bool empty = T == 0 || T > 0xffffffffull;
+  const float invT = 1.0f / (float)T;
+  uint32_t col = 0;
+  unsigned long long ci = 0, cii = 0;
+  double energy = 0.0, ent = 0.0, homog = 0.0;     // rows 0 .. 7 (or the lane's fourth)
+  double energy1 = 0.0, ent1 = 0.0, homog1 = 0.0;  // rows 8 .. 15
+  for (uint32_t i = begin; i < end; i += U) {
+    uint32_t c[U];
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u) c[u] = live && !empty && i + u < N ? P[(i + u) * N + j] : 0u;
+    double fe = 0.0, fn = 0.0, fh = 0.0;
+    uint32_t r = i;
+#pragma unroll 1
+    for (; r < i + U; ++r) {  // (not unrolled: short code, for the instruction cache)
+      const uint32_t cr = c[0];
+      c[0] = c[1];
+      c[1] = c[2];
+      c[2] = c[3];
+      if (cr == 0u) continue;
+      col += cr;
+      ci += (unsigned long long)r * cr;
+      cii += (unsigned long long)(r * r) * cr;
+      const float p = (float)cr * invT;
+      fe += (double)(p * p);
+      const float lp = (2ull * cr > T) ? log1pf(-(float)(T - cr) * invT) : logf(p);
+      fn -= (double)(p * lp);
+      const uint32_t d = r > j ? r - j : j - r;
+      fh += (double)(p / (1.0f + (float)(d * d)));
+    }
+    const bool upper = !wide && i >= 2u * U;
+    energy += upper ? 0.0 : fe;
+    ent += upper ? 0.0 : fn;
+    homog += upper ? 0.0 : fh;
+    energy1 += upper ? fe : 0.0;
+    ent1 += upper ? fn : 0.0;
+    homog1 += upper ? fh : 0.0;
+  }
+  FeatureSums s;
+  if (wide) {  // the four fourths
+    energy = sum_xor16(energy);
+    ent = sum_xor16(ent);
+    homog = sum_xor16(homog);
+    energy1 = __shfl_xor(energy, 32);
+    ent1 = __shfl_xor(ent, 32);
+    homog1 = __shfl_xor(homog, 32);
+    col = (uint32_t)__shfl_xor((int)col, 16) + col;
+    col = (uint32_t)__shfl_xor((int)col, 32) + col;
+    ci = sum_xor32(sum_xor16((uint64_t)ci));
+    cii = sum_xor32(sum_xor16((uint64_t)cii));
+  }
+  s.energy = row16_sum(energy + energy1);
+  s.ent = row16_sum(ent + ent1);
+  s.homog = row16_sum(homog + homog1);
+  s.si = row16_sum(ci);
+  s.sii = row16_sum(cii);
+  s.sij = row16_sum((unsigned long long)j * ci);
+  s.sj = row16_sum((unsigned long long)j * col);
+  s.sjj = row16_sum((unsigned long long)(j * j) * col);
+  if ((int)mine >= count || (wide && q != 0u)) return;
+  if (empty) {
+    if (j < 5) o[5u * mine + j] = T == 0 ? 0.0f : __builtin_nanf("");
+  } else if (j == 0) {
+    features_store(T, s, o + 5u * mine);
+  }
+}
+
+// N > 16: by one wavefront that plays all of features_waves(N), with no LDS and
+// no barrier.  Every lane must call it; lane 0 writes o.
 __device__ __forceinline__ void glcm_features_wave(const uint32_t* P, uint32_t N, float* o) {
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t W = (uint32_t)features_waves((int)N);
@@ -156,6 +242,14 @@ __device__ __forceinline__ void glcm_features_wave(const uint32_t* P, uint32_t N
   FeatureSums a = {0, 0, 0, 0, 0, 0.0, 0.0, 0.0};
   for (uint32_t w = 0; w < W; ++w) features_add(a, features_sums(P, N, T, invT, w, W));
   if (lane == 0) features_store(T, a, o);
+}
+
+// One GLCM's statistics by one wavefront.
+__device__ __forceinline__ void glcm_features_any(const uint32_t* P, uint32_t N, float* o) {
+  if (N <= kFeatures16)
+    glcm_features_16(P, N, 1, true, o);
+  else
+    glcm_features_wave(P, N, o);
 }
 
 }  // namespace

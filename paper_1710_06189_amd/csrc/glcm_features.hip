@@ -22,8 +22,7 @@ __global__ __launch_bounds__(64 * W) void k_features(const uint32_t* glcm, int N
 // N <= 32: one wavefront per GLCM, four per workgroup.
 __global__ __launch_bounds__(256) void k_features_wave(const uint32_t* glcm, int K, int N, float* out) {
   const int k = blockIdx.x * 4 + (int)(threadIdx.x >> 6);
-  if (k >= K) return;
-  glcm_features_wave(glcm + (size_t)k * (uint32_t)N * (uint32_t)N, (uint32_t)N, out + (size_t)k * 5);
+  if (k < K) glcm_features_any(glcm + (size_t)k * (uint32_t)N * (uint32_t)N, (uint32_t)N, out + (size_t)k * 5);
 }
 
 }  // namespace

@@ -137,14 +137,17 @@ struct BatchArgs {
   int K;                               // offsets, <= kStripMaxKp
   int32_t dx[kStripMaxKp], dy[kStripMaxKp];  // offsets as given (per-pixel path)
   int32_t vcode[kStripMaxKp];          // canonical codes (strip path), as in VoteArgs
+  int32_t slot[kStripMaxKp];           // slots of the matrix-core kernel (onehot_slot)
   unsigned long long tmask;            // bit k: offset k counted as its opposite, stored transposed
   uint32_t pitch;                      // N + 1
   int min_rows;                        // shortest row segment a lane walks
   const BatchTile* tiles;              // [nitems], largest first
   const BatchFin* fins;                // [nfins] images split into bands
   uint32_t* partials;                  // [band slots][K][N][N] partial counts of the bands
-  uint32_t* counter;                   // next item (zero at launch and again at the end)
+  uint32_t* counter;                   // next item (zero at launch and again at the end); the
+                                       // matrix-core kernel has a second for its small items
   int nitems, nfins;
+  int nbig;                            // matrix-core kernel: items that a whole workgroup takes
   uint32_t* out;                       // [T][K][N][N]
   float* feat;                         // [T][K][5] or null
   // or, when outs is set, image t's counts go to outs[t] ([K][N][N]) and its
@@ -193,6 +196,10 @@ hipError_t launch_vote_blocks(const BlockArgs& a, int dtype_bytes, int wg, hipSt
 hipError_t launch_batch(const BatchArgs& a, int T, int dtype_bytes, int maxdy, int D, int wg, size_t lds_bytes,
                         hipStream_t stream);
 constexpr int kBatchThreads = 256;
+// The same on the matrix cores: N <= 16, offsets with slots at a reach of
+// maxdy = 1 or 2; T workgroups of kBatchThreads.
+hipError_t launch_batch_onehot(const BatchArgs& a, int T, int dtype_bytes, int maxdy, hipStream_t stream);
+constexpr int kBatchOnehotPerCu = 4;  // workgroups a CU holds (registers)
 // Sums the bands of the F split images into out (and their statistics);
 // nothing is launched when F = 0.
 hipError_t launch_batch_fin(const BatchArgs& a, int F, hipStream_t stream);

@@ -107,3 +107,44 @@ def test_batches(dtype, name, N):
     finally:
         torch.cuda.synchronize()
         plan.close()
+
+
+@pytest.mark.parametrize("name,N", [("d1", 16), ("some of d2", 7)])
+def test_many_images(name, N):
+    """More images than workgroups: the small ones are counted by a wavefront
+    each, next to large ones, 2^13 pixels (the line between them) on both
+    sides; the LDS kernel gives the same bits."""
+    offs = SETS[name][:4]
+    big = synth.smooth(700, 801, 3.0, 13, np.uint8)
+    g = np.random.default_rng(14)
+    shapes = [(1, 1), (64, 127), (64, 128), (64, 129), (128, 64), (300, 310), (600, 790), (1, 60), (60, 1)]
+    shapes += [tuple(int(v) for v in g.integers(1, 100, 2)) for _ in range(1291)]
+    src = dev(big)
+    views = [src[y % 50:y % 50 + h, y % 11:y % 11 + w] for y, (h, w) in enumerate(shapes)]
+    plan = G.glcm_plan_create(np.uint8, N, offs, 801, 700)
+    try:
+        batch = G.PreparedBatch(views, plan)
+        for _ in range(3):
+            P, F = batch.run(20, 230, features=True)
+        for y in [*range(9), *range(9, 1300, 97)]:
+            h, w = shapes[y]
+            assert np.array_equal(host(P[y]), oracle.glcm(big[y % 50:y % 50 + h, y % 11:y % 11 + w], N, 20, 230, offs)), (h, w)
+        plan.set_batch_tuning(replicas=8)
+        P2, F2 = G.glcm_batch_compute(views, plan, 20, 230)
+        assert torch.equal(P.view(torch.int32), P2.view(torch.int32)) and torch.equal(F.view(torch.int32), F2.view(torch.int32))
+    finally:
+        torch.cuda.synchronize()
+        plan.close()
+
+
+@pytest.mark.parametrize("W", [1 << 19, (1 << 19) + 1])
+def test_widest_images(W):
+    """Images too wide for the matrix cores' sums go to the LDS kernel."""
+    img = synth.uniform(2, W, 15, np.uint8)
+    plan = G.glcm_plan_create(np.uint8, 16, D1, W, 2)
+    try:
+        P, _ = G.glcm_batch_compute([dev(img), dev(img)], plan, 0, 255)
+        assert np.array_equal(host(P[1]), oracle.glcm(img, 16, 0, 255, D1))
+    finally:
+        torch.cuda.synchronize()
+        plan.close()
