@@ -929,7 +929,6 @@ int count_device(glcm_plan_t p, const void* img, int W, int H, int64_t stride, i
   // x / N and x / N^2 as multiply-high + shift: make_quant(1, 0, d - 1) has
   // D = d and the same division constants
   a.div_n = make_quant(1, 0, (uint32_t)p->N - 1);
-  a.div_nn = make_quant(1, 0, NN - 1);
   fast_quant(b, p->N, lo, hi, &a.qfast, &a.qfast_shift, &a.qfast_mask);
   a.K = p->K;
   a.words_total = words;

@@ -57,7 +57,7 @@ struct VoteArgs {
   int region_rows;            // first-pixel rows per band
   int rows_per_wave;          // row kernel: first-pixel rows per wavefront slab (4)
   uint32_t pitch;             // row kernel: LDS row pitch of a GLCM, >= N + 1 (row/column N: sentinel)
-  Quant div_n, div_nn;        // magic/shift for dividing by N and by N*N (only those fields used)
+  Quant div_n;                // magic/shift for dividing by N (only those fields used)
   int c16;                    // slab kernel: 16-bit counters, two copies per dword; strip kernel:
                               // 16-bit counters, two GLCMs per dword
   int kp;                     // strip kernel: GLCMs per partition (<= 4)

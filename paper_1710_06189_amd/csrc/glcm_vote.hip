@@ -9,7 +9,6 @@
 // different banks.  The merge of all copies into one result (the final sum in
 // Section II.A) takes two steps: every workgroup writes its band's counts to
 // a partial buffer, and a second kernel sums the partials into `out`.
-#include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -17,67 +16,10 @@
 
 #include "glcm_device.h"
 #include "glcm_internal.h"
+#include "glcm_merge.h"
 
 namespace glcm {
 namespace {
-
-// ---------------------------------------------------------------------------
-// Merge of the LDS copies (the final sum of Section II.A), in two steps that
-// need no synchronisation between workgroups inside a kernel:
-//
-//  * merge = per-XCD accumulation: every workgroup adds its non-zero counts to
-//    the accumulation slice of the XCD it runs on (hardware register XCC_ID),
-//    with workgroup-scope atomics, which execute in that XCD's L2 (all CUs of
-//    an XCD share it, and no other XCD touches the slice).  The kernel
-//    boundary writes the L2s back; k_finish sums the slices into `out` and
-//    clears them for the next launch.
-//  * merge = band partials: every workgroup stores its counts to its own row
-//    of a partial buffer and k_reduce sums the rows.
-//
-// The LDS matrices may be padded: word (k, i, j) of the partition (k counted
-// from the partition's first GLCM) sits at copy-block k * nn1 + i * n1 + j,
-// each block holding R copies (R / 2 dwords with 16-bit counters).
-// ---------------------------------------------------------------------------
-__device__ void store_partial(const VoteArgs& a, const uint32_t* lds, uint32_t pbase, uint32_t pwords, int region,
-                              uint32_t n1, uint32_t nn1, bool c16) {
-  __syncthreads();
-  const uint32_t R = 1u << a.log2R;
-  const uint32_t D = c16 ? R / 2u : R;  // dwords per bin (a multiple of 4 when D >= 4)
-  const uint32_t N = a.q.nlev, NN = N * N;
-  uint32_t* dst = a.partials + (size_t)region * a.words_total + pbase;
-  for (uint32_t w = threadIdx.x; w < pwords; w += blockDim.x) {
-    uint32_t src = w;
-    if (n1 != N) {
-      const uint32_t k = divide(w, a.div_nn.magic, a.div_nn.shift), rem = w - k * NN;
-      const uint32_t i = divide(rem, a.div_n.magic, a.div_n.shift), j = rem - i * N;
-      src = k * nn1 + i * n1 + j;
-    }
-    const uint32_t* c = lds + src * D;
-    uint32_t s = 0;
-    if (D >= 4) {
-      for (uint32_t d = 0; d < D; d += 4) {
-        const uint4 v = *(const uint4*)(c + d);
-        s += c16 ? (v.x & 0xffffu) + (v.x >> 16) + (v.y & 0xffffu) + (v.y >> 16) + (v.z & 0xffffu) + (v.z >> 16) +
-                       (v.w & 0xffffu) + (v.w >> 16)
-                 : (v.x + v.y) + (v.z + v.w);
-      }
-    } else if (c16) {
-      for (uint32_t d = 0; d < D; ++d) s += (c[d] & 0xffffu) + (c[d] >> 16);
-    } else {
-      for (uint32_t d = 0; d < D; ++d) s += c[d];
-    }
-    if (a.xbuf) {
-      if (s) {
-        uint32_t xcc;
-        asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID, 0, 4)" : "=s"(xcc));
-        __hip_atomic_fetch_add(a.xbuf + (size_t)(xcc & (kXcdSlots - 1u)) * a.words_total + pbase + w, s,
-                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      }
-    } else {
-      dst[w] = s;
-    }
-  }
-}
 
 // out[w] = (accumulate ? out[w] : 0) + sum of the first nslots accumulation
 // slices (the others stay zero); clears them.
@@ -167,23 +109,6 @@ __global__ __launch_bounds__(kReduceQuads * kReduceGroups) void k_reduce(const u
     const uint32_t r[4] = {t.x, t.y, t.z, t.w};
     for (int e = 0; e < 4 && w + e < M; ++e) out[w + e] = (accumulate ? out[w + e] : 0u) + r[e];
   }
-}
-
-// Workgroup -> (band, partition).  Workgroups go to the XCDs round-robin
-// (workgroup b runs on XCD b mod 8), and every partition of a band reads the
-// band's rows: keeping the partitions of one band on one XCD lets its L2
-// serve the second read instead of HBM.  Workgroup b = 8 s + x takes
-// partition s mod P of band 8 (s / P) + x for the first 8 floor(nregions / 8)
-// bands; the remaining bands take the plain order (a bijection either way).
-constexpr int kXcds = 8;
-__device__ __forceinline__ int2 band_of_block(int b, int P, int nregions) {
-  const int full = nregions / kXcds * kXcds;
-  if (P > 1 && b < full * P) {
-    const int x = b % kXcds, s = b / kXcds;
-    return make_int2(s / P * kXcds + x, s % P);
-  }
-  const int r = b - full * P;
-  return make_int2(full + r / P, r % P);
 }
 
 // ---------------------------------------------------------------------------
@@ -308,7 +233,7 @@ __global__ __launch_bounds__(1024) void k_vote_generic(VoteArgs a) {
       }
     }
   }
-  store_partial(a, lds, pbase, pwords, region, a.q.nlev, a.q.nlev * a.q.nlev, false);
+  store_partial(a, lds, pbase, pwords, region);
 }
 
 // ---------------------------------------------------------------------------
@@ -375,196 +300,6 @@ __global__ __launch_bounds__(256) void k_vote_l2(VoteArgs a) {
       }
     }
   }
-}
-
-// ---------------------------------------------------------------------------
-// Row kernel: the fast path for aligned images (base and row pitch multiples
-// of 16 bytes), N <= 255, offsets with |dx| <= 4 and 0 <= dy <= MAXDY <= 4 after
-// canonicalisation (an offset with dy < 0 is counted as its opposite and voted
-// transposed).  Each lane owns a 16-pixel column chunk; a wavefront covers 64
-// chunks (1024 pixels) of RPW consecutive rows (a slab).  All RPW + MAXDY rows
-// of the slab are loaded at once, quantized into bytes, and the horizontal
-// neighbours come from the adjacent lanes through DPP wave shifts, so each
-// pixel is read from memory once per slab.
-//
-// Pixels outside the image (x < 0, x >= W, or rows >= H) get the sentinel
-// level N.  The LDS copy of each GLCM is (N+1) x (N+1); votes touching a
-// sentinel land in row or column N and are dropped by the merge, so the vote
-// loop carries no bounds checks at all.
-// ---------------------------------------------------------------------------
-struct Ring {
-  uint32_t w[6];  // [left halo (4 px) | 16 px chunk | right halo (4 px)], one level per byte
-};
-
-// UNAL: a row of an image whose base or pitch is not 16-byte aligned, read in
-// place as the dwords that hold it (load_row_unaligned; only the wave-boundary
-// lanes read halo dwords, the only ones finish_row uses).
-template <typename Pix, bool UNAL>
-__device__ __forceinline__ void issue_row(RawChunk<Pix>& rc, const VoteArgs& a, int y, int x0, int lane) {
-#pragma unroll
-  for (int h = 0; h < (int)sizeof(Pix); ++h) {
-    rc.v[h] = make_uint4(0u, 0u, 0u, 0u);
-    rc.lh[h] = 0u;
-    rc.rh[h] = 0u;
-  }
-  if (y >= a.H) return;
-  if constexpr (UNAL) {
-    load_row_unaligned<Pix, false>(rc, Geom{a.img, a.stride, a.W, a.H}, y, x0);
-    return;
-  }
-  const Pix* row = (const Pix*)a.img + (int64_t)y * a.stride;
-  if (x0 < a.W) rc.v[0] = *(const uint4*)(row + x0);
-  if (sizeof(Pix) == 2 && x0 + 8 < a.W) rc.v[sizeof(Pix) - 1] = *(const uint4*)(row + x0 + 8);
-  if (lane == 0 && x0 >= 16 && x0 - 4 < a.W) {
-    if (sizeof(Pix) == 1) rc.lh[0] = *(const uint32_t*)(row + x0 - 4);
-    else { const uint2 t = *(const uint2*)(row + x0 - 4); rc.lh[0] = t.x; rc.lh[sizeof(Pix) - 1] = t.y; }
-  }
-  if (lane == 63 && x0 + 16 < a.W) {
-    if (sizeof(Pix) == 1) rc.rh[0] = *(const uint32_t*)(row + x0 + 16);
-    else { const uint2 t = *(const uint2*)(row + x0 + 16); rc.rh[0] = t.x; rc.rh[sizeof(Pix) - 1] = t.y; }
-  }
-}
-
-template <typename Pix>
-__device__ __forceinline__ void finish_row(Ring& rg, const RawChunk<Pix>& rc, const VoteArgs& a, int y, int x0,
-                                           int lane, uint32_t sent4) {
-  uint32_t c[4], lh, rh;
-  if (sizeof(Pix) == 1) {
-    c[0] = quant4_u8(rc.v[0].x, a); c[1] = quant4_u8(rc.v[0].y, a);
-    c[2] = quant4_u8(rc.v[0].z, a); c[3] = quant4_u8(rc.v[0].w, a);
-    lh = quant4_u8(rc.lh[0], a);
-    rh = quant4_u8(rc.rh[0], a);
-  } else {
-    c[0] = quant4_u16(rc.v[0].x, rc.v[0].y, a); c[1] = quant4_u16(rc.v[0].z, rc.v[0].w, a);
-    c[2] = quant4_u16(rc.v[sizeof(Pix) - 1].x, rc.v[sizeof(Pix) - 1].y, a);
-    c[3] = quant4_u16(rc.v[sizeof(Pix) - 1].z, rc.v[sizeof(Pix) - 1].w, a);
-    lh = quant4_u16(rc.lh[0], rc.lh[sizeof(Pix) - 1], a);
-    rh = quant4_u16(rc.rh[0], rc.rh[sizeof(Pix) - 1], a);
-  }
-  if (y >= a.H) {
-    c[0] = c[1] = c[2] = c[3] = sent4;
-  } else {
-#pragma unroll
-    for (int m = 0; m < 4; ++m) c[m] = clip_dword(c[m], x0 + 4 * m, a.W, sent4);
-  }
-  const uint32_t from_left = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)c[3], kDppWaveShr1, 0xf, 0xf, false);
-  const uint32_t from_right = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)c[0], kDppWaveShl1, 0xf, 0xf, false);
-  // wave-boundary lanes take the halo they loaded themselves (sentinel outside the image)
-  lh = (y < a.H && x0 >= 16) ? clip_dword(lh, x0 - 4, a.W, sent4) : sent4;
-  rh = (y < a.H) ? clip_dword(rh, x0 + 16, a.W, sent4) : sent4;
-  rg.w[0] = lane == 0 ? lh : from_left;
-  rg.w[1] = c[0]; rg.w[2] = c[1]; rg.w[3] = c[2]; rg.w[4] = c[3];
-  rg.w[5] = lane == 63 ? rh : from_right;
-}
-
-// Second-pixel levels of the 16 chunk pixels for horizontal shift dx in [-4, 4]:
-// bytes 4+dx .. 19+dx of the 24-byte ring row, as a funnel shift of 64-bit
-// values (no indexed register access, which the compiler would spill).
-__device__ __forceinline__ void window(const Ring& rg, int dx, uint32_t out[4]) {
-  const uint64_t r0 = (uint64_t)rg.w[0] | ((uint64_t)rg.w[1] << 32);
-  const uint64_t r1 = (uint64_t)rg.w[2] | ((uint64_t)rg.w[3] << 32);
-  const uint64_t r2 = (uint64_t)rg.w[4] | ((uint64_t)rg.w[5] << 32);
-  const uint32_t sh = (uint32_t)(4 + dx) * 8u;  // 0 .. 64
-  uint64_t lo, hi;
-  if (sh == 0) {
-    lo = r0; hi = r1;
-  } else if (sh == 64) {
-    lo = r1; hi = r2;
-  } else {
-    lo = (r0 >> sh) | (r1 << (64u - sh));
-    hi = (r1 >> sh) | (r2 << (64u - sh));
-  }
-  out[0] = (uint32_t)lo; out[1] = (uint32_t)(lo >> 32);
-  out[2] = (uint32_t)hi; out[3] = (uint32_t)(hi >> 32);
-}
-
-// Votes of one offset whose canonical dy is S, for the RPW first-pixel rows of
-// the slab: LDS byte address = C + a * MA + b * MB.
-template <int S, int RPW, int NROWS>
-__device__ __forceinline__ void vote_offset(uint32_t* lds, const Ring (&rows)[NROWS], int nrows_first, int dx,
-                                            uint32_t C, uint32_t MA, uint32_t MB, uint32_t inc) {
-#pragma unroll
-  for (int i = 0; i < RPW; ++i) {
-    if (i < nrows_first) {
-      uint32_t b[4];
-      window(rows[i + S], dx, b);
-      const uint32_t f[4] = {rows[i].w[1], rows[i].w[2], rows[i].w[3], rows[i].w[4]};
-#pragma unroll
-      for (int t = 0; t < 16; ++t) {
-        const uint32_t av = (f[t >> 2] >> ((t & 3) * 8)) & 0xffu;
-        const uint32_t bv = (b[t >> 2] >> ((t & 3) * 8)) & 0xffu;
-        const uint32_t addr = C + __umul24(av, MA) + __umul24(bv, MB);  // full-rate 24-bit multiplies
-        __hip_atomic_fetch_add((uint32_t*)((char*)lds + addr), inc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      }
-    }
-  }
-}
-
-template <typename Pix, int MAXDY, int RPW, bool UNAL>
-__global__ __launch_bounds__(rows_max_threads(sizeof(Pix), MAXDY, UNAL)) void k_vote_rows(VoteArgs a) {
-  extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
-  const int2 rp = band_of_block(blockIdx.x, a.P, a.nregions);
-  const int region = rp.x, part = rp.y;
-  const uint32_t N = a.q.nlev, N1 = a.pitch, NN = N * N, NN1 = N1 * N1;
-  // Partitions of the row kernel are groups of whole GLCMs (offsets).
-  const uint32_t pbase = (uint32_t)part * a.part_words;
-  const uint32_t pwords = min(a.part_words, a.words_total - pbase);
-  const int kp0 = (int)(pbase / NN), kp1 = (int)((pbase + pwords) / NN);
-  // Counters: R copies per bin, 32 bits each, or 16 bits each (copies 2m and
-  // 2m+1 share a dword) when the host has bounded every count below 2^16.
-  const uint32_t R = 1u << a.log2R;
-  const uint32_t dwords_per_bin = a.c16 ? R / 2u : R;
-  zero_lds(lds, (uint32_t)(kp1 - kp0) * NN1 * dwords_per_bin);
-  __syncthreads();
-
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
-  // This thread's dword of a bin is lane mod D (D = dwords per bin): lanes
-  // sharing a dword are D chunks (16 D pixels) apart, so on smooth images they
-  // rarely vote the same bin; with 16-bit counters the half is bit log2(D).
-  const uint32_t D = dwords_per_bin;
-  const uint32_t g = threadIdx.x & (D - 1u);
-  const uint32_t h = (threadIdx.x / D) & 1u;
-  const uint32_t B = D * 4u;  // bytes per bin (all copies)
-  const uint32_t Cr = g * 4u;
-  const uint32_t inc = a.c16 ? (1u << (h * 16u)) : 1u;
-  const uint32_t sent4 = N * 0x01010101u;
-  const int y0 = a.y_begin + region * a.region_rows;
-  const int y1 = min(a.y_end, y0 + a.region_rows);
-  const int chunks = (a.W + 15) >> 4;
-  const int spans = (chunks + 63) >> 6;
-  const int bands = y1 > y0 ? (y1 - y0 + RPW - 1) / RPW : 0;
-  constexpr int NROWS = RPW + MAXDY;
-
-  for (int slab = wave; slab < spans * bands; slab += nwaves) {
-    const int span = slab % spans, band = slab / spans;
-    const int x0 = ((span << 6) + lane) << 4;
-    const int ys = y0 + band * RPW;
-    const int nfirst = min(RPW, y1 - ys);
-    Ring rows[NROWS];
-    {
-      RawChunk<Pix> raw[NROWS];
-#pragma unroll
-      for (int i = 0; i < NROWS; ++i) issue_row<Pix, UNAL>(raw[i], a, ys + i, x0, lane);
-#pragma unroll
-      for (int i = 0; i < NROWS; ++i) finish_row<Pix>(rows[i], raw[i], a, ys + i, x0, lane, sent4);
-    }
-    for (int k = kp0; k < kp1; ++k) {
-      const int dy = a.dy[k], dx = a.dx[k];
-      const bool tr = (a.tmask >> k) & 1ull;
-      const uint32_t C = (uint32_t)(k - kp0) * NN1 * B + Cr;
-      const uint32_t MA = tr ? B : N1 * B, MB = tr ? N1 * B : B;
-      switch (dy) {
-        case 0: vote_offset<0, RPW>(lds, rows, nfirst, dx, C, MA, MB, inc); break;
-        case 1: if (MAXDY >= 1) vote_offset<(MAXDY >= 1 ? 1 : 0), RPW>(lds, rows, nfirst, dx, C, MA, MB, inc); break;
-        case 2: if (MAXDY >= 2) vote_offset<(MAXDY >= 2 ? 2 : 0), RPW>(lds, rows, nfirst, dx, C, MA, MB, inc); break;
-        case 3: if (MAXDY >= 3) vote_offset<(MAXDY >= 3 ? 3 : 0), RPW>(lds, rows, nfirst, dx, C, MA, MB, inc); break;
-        case 4: if (MAXDY >= 4) vote_offset<(MAXDY >= 4 ? 4 : 0), RPW>(lds, rows, nfirst, dx, C, MA, MB, inc); break;
-        default: break;  // the host never launches an offset with dy > MAXDY
-      }
-    }
-  }
-  store_partial(a, lds, pbase, pwords, region, N1, NN1, a.c16 != 0);
 }
 
 // One first-pixel row of a strip: bases, votes of every GLCM of the
@@ -763,45 +498,11 @@ __global__ __launch_bounds__(strip_max_threads(sizeof(Pix), MAXDY)) void k_vote_
 
 }  // namespace
 
-template <typename K>
-static hipError_t launch(K kernel, const VoteArgs& a, dim3 grid, dim3 block, size_t lds_bytes, hipStream_t stream,
-                         const LaunchTiming& tm) {
-  // with events, the dispatch itself stamps the kernel's start and end
-  hipExtLaunchKernelGGL(kernel, grid, block, (uint32_t)lds_bytes, stream, tm.start, tm.stop, 0u, a);
-  return hipGetLastError();
-}
-
 hipError_t launch_vote_generic(const VoteArgs& a, int dtype_bytes, int wg, size_t lds_bytes, hipStream_t stream,
                                const LaunchTiming& tm) {
   const dim3 grid(a.nregions * a.P), block(wg);
   if (dtype_bytes == 1) return launch(k_vote_generic<uint8_t>, a, grid, block, lds_bytes, stream, tm);
   return launch(k_vote_generic<uint16_t>, a, grid, block, lds_bytes, stream, tm);
-}
-
-template <typename Pix, bool UNAL>
-static hipError_t launch_rows_u(const VoteArgs& a, int maxdy, int wg, size_t lds_bytes, hipStream_t stream,
-                                const LaunchTiming& tm) {
-  const dim3 grid(a.nregions * a.P), block(wg);
-  switch (maxdy) {
-    case 1: return launch(k_vote_rows<Pix, 1, 4, UNAL>, a, grid, block, lds_bytes, stream, tm);
-    case 2: return launch(k_vote_rows<Pix, 2, 4, UNAL>, a, grid, block, lds_bytes, stream, tm);
-    case 4: return launch(k_vote_rows<Pix, 4, 4, UNAL>, a, grid, block, lds_bytes, stream, tm);
-    default: return hipErrorInvalidValue;
-  }
-}
-
-template <typename Pix>
-static hipError_t launch_rows_t(const VoteArgs& a, int maxdy, int wg, size_t lds_bytes, hipStream_t stream,
-                               const LaunchTiming& tm) {
-  return a.unaligned ? launch_rows_u<Pix, true>(a, maxdy, wg, lds_bytes, stream, tm)
-                     : launch_rows_u<Pix, false>(a, maxdy, wg, lds_bytes, stream, tm);
-}
-
-hipError_t launch_vote_rows(const VoteArgs& a, int dtype_bytes, int maxdy, int rpw, int wg, size_t lds_bytes,
-                            hipStream_t stream, const LaunchTiming& tm) {
-  if (rpw != 4) return hipErrorInvalidValue;
-  return dtype_bytes == 1 ? launch_rows_t<uint8_t>(a, maxdy, wg, lds_bytes, stream, tm)
-                          : launch_rows_t<uint16_t>(a, maxdy, wg, lds_bytes, stream, tm);
 }
 
 template <typename Pix, int MAXDY, bool PAIR, bool UNAL>
