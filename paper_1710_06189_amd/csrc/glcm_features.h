@@ -20,13 +20,17 @@ namespace {
 // at a time (64 columns of one row when N > 64) and a lane keeps its column, so
 // sum c, sum i c and sum i^2 c per column are all the integers a bin adds to;
 // the rest follows once at the end (sum j c = j sum c and so on, and
-// sum (i - j)^2 c = sum i^2 c + sum j^2 c - 2 sum i j c).  The fp64 sums of a
-// wavefront meet by lane exchanges and those of the W wavefronts are added in
-// order, so the result depends on W, not on which wavefronts did the work: one
-// wavefront that plays all W (glcm_features_wave) gives the same bits as W of
-// them (glcm_features_wg).
+// sum (i - j)^2 c = sum i^2 c + sum j^2 c - 2 sum i j c).  A lane's fp64 sums of
+// the W wavefronts are added in order and the lanes then meet by exchanges, so
+// the result depends on W, not on which wavefronts did the work: one wavefront
+// that plays all W (glcm_features_wave) gives the same bits as W of them
+// (glcm_features_wg).  Bound: latency of the loads and of the one reduction up
+// to N = 128, the logarithms of the one CU that holds the matrix above.
+// Measured on MI355X, 7 matrices of N = 64: 11.5 us with 4 wavefronts that each
+// reduce their own sums, 7.1 with 16 and one reduction; 12 of N = 256: 36.8 and
+// 35.8.  Up to N = 48 four wavefronts leave a lane at most 12 bins.
 // ---------------------------------------------------------------------------
-constexpr int features_waves(int N) { return N <= 32 ? 1 : (N <= 128 ? 4 : 16); }
+constexpr int features_waves(int N) { return N <= 32 ? 1 : (N <= 48 ? 4 : 16); }
 
 struct FeatureSums {
   unsigned long long si, sii, sij, sj, sjj;
@@ -58,7 +62,7 @@ __device__ __forceinline__ unsigned long long features_total(const uint32_t* P, 
   return wave_sum(T);
 }
 
-// The sums of wavefront w of W (T below 2^32).
+// This lane's share of the sums of wavefront w of W (T below 2^32).
 __device__ __forceinline__ FeatureSums features_sums(const uint32_t* P, uint32_t N, unsigned long long T, float invT,
                                                      uint32_t w, uint32_t W) {
   const uint32_t lane = threadIdx.x & 63u;
@@ -99,47 +103,62 @@ __device__ __forceinline__ FeatureSums features_sums(const uint32_t* P, uint32_t
     s.sj += (unsigned long long)j * col;
     s.sjj += (unsigned long long)(j * j) * col;
   }
-  s.si = wave_sum(s.si);
-  s.sii = wave_sum(s.sii);
-  s.sij = wave_sum(s.sij);
-  s.sj = wave_sum(s.sj);
-  s.sjj = wave_sum(s.sjj);
-  s.energy = wave_sum(s.energy);
-  s.ent = wave_sum(s.ent);
-  s.homog = wave_sum(s.homog);
   return s;
 }
 
-__device__ __forceinline__ void features_add(FeatureSums& a, const FeatureSums& b) {
-  a.si += b.si; a.sii += b.sii; a.sij += b.sij; a.sj += b.sj; a.sjj += b.sjj;
-  a.energy += b.energy; a.ent += b.ent; a.homog += b.homog;
+// The lanes' shares, on every lane.
+__device__ __forceinline__ FeatureSums features_reduce(const FeatureSums& s) {
+  return {wave_sum(s.si), wave_sum(s.sii), wave_sum(s.sij), wave_sum(s.sj), wave_sum(s.sjj),
+          wave_sum(s.energy), wave_sum(s.ent), wave_sum(s.homog)};
 }
 
-// By a workgroup of W wavefronts (W = features_waves(N)): two barriers.  redu:
-// W totals, reds: W sums of workgroup scratch.  Every thread of the workgroup
-// must call it.
+struct FeatureShare {  // scratch of a workgroup of W wavefronts
+  unsigned long long total, ints[5];
+  double energy[64], ent[64], homog[64];  // a lane's
+};
+
+// By a workgroup of W wavefronts (W = features_waves(N)): two barriers.  Every
+// thread of the workgroup must call it.
 template <int W>
-__device__ __forceinline__ void glcm_features_wg(const uint32_t* P, uint32_t N, float* o, unsigned long long* redu,
-                                                 FeatureSums* reds) {
+__device__ __forceinline__ void glcm_features_wg(const uint32_t* P, uint32_t N, float* o, FeatureShare* share) {
   const uint32_t w = threadIdx.x >> 6, lane = threadIdx.x & 63u;
   unsigned long long T = features_total(P, N * N, w, W);
-  if (lane == 0) redu[w] = T;
+  if (lane == 0) share[w].total = T;
   __syncthreads();
   T = 0;
 #pragma unroll
-  for (int x = 0; x < W; ++x) T += redu[x];
+  for (int x = 0; x < W; ++x) T += share[x].total;
   if (T == 0 || T > 0xffffffffull) {
     if (threadIdx.x < 5) o[threadIdx.x] = T == 0 ? 0.0f : __builtin_nanf("");
     return;
   }
-  const FeatureSums s = features_sums(P, N, T, 1.0f / (float)T, w, W);
-  if (lane == 0) reds[w] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    FeatureSums a = {0, 0, 0, 0, 0, 0.0, 0.0, 0.0};
-    for (int x = 0; x < W; ++x) features_add(a, reds[x]);
-    features_store(T, a, o);
+  FeatureSums s = features_sums(P, N, T, 1.0f / (float)T, w, W);
+  const unsigned long long ints[5] = {wave_sum(s.si), wave_sum(s.sii), wave_sum(s.sij), wave_sum(s.sj), wave_sum(s.sjj)};
+  if (lane == 0) {
+#pragma unroll
+    for (int q = 0; q < 5; ++q) share[w].ints[q] = ints[q];
   }
+  share[w].energy[lane] = s.energy;
+  share[w].ent[lane] = s.ent;
+  share[w].homog[lane] = s.homog;
+  __syncthreads();
+  if (w != 0) return;
+  s = {0, 0, 0, 0, 0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int x = 0; x < W; ++x) {
+    s.energy += share[x].energy[lane];
+    s.ent += share[x].ent[lane];
+    s.homog += share[x].homog[lane];
+  }
+  if (lane < (uint32_t)W) {
+    s.si = share[lane].ints[0];
+    s.sii = share[lane].ints[1];
+    s.sij = share[lane].ints[2];
+    s.sj = share[lane].ints[3];
+    s.sjj = share[lane].ints[4];
+  }
+  s = features_reduce(s);
+  if (lane == 0) features_store(T, s, o);
 }
 
 // N <= 16, by one wavefront: each group of 16 lanes keeps a column a lane.
@@ -240,7 +259,12 @@ __device__ __forceinline__ void glcm_features_wave(const uint32_t* P, uint32_t N
   }
   const float invT = 1.0f / (float)T;
   FeatureSums a = {0, 0, 0, 0, 0, 0.0, 0.0, 0.0};
-  for (uint32_t w = 0; w < W; ++w) features_add(a, features_sums(P, N, T, invT, w, W));
+  for (uint32_t w = 0; w < W; ++w) {
+    const FeatureSums s = features_sums(P, N, T, invT, w, W);
+    a = {a.si + s.si, a.sii + s.sii, a.sij + s.sij, a.sj + s.sj, a.sjj + s.sjj,
+         a.energy + s.energy, a.ent + s.ent, a.homog + s.homog};
+  }
+  a = features_reduce(a);
   if (lane == 0) features_store(T, a, o);
 }
 

@@ -13,10 +13,9 @@ namespace {
 // N > 32: one workgroup of W wavefronts per GLCM.
 template <int W>
 __global__ __launch_bounds__(64 * W) void k_features(const uint32_t* glcm, int N, float* out) {
-  __shared__ unsigned long long redu[W];
-  __shared__ FeatureSums reds[W];
+  __shared__ FeatureShare share[W];
   glcm_features_wg<W>(glcm + (size_t)blockIdx.x * (uint32_t)N * (uint32_t)N, (uint32_t)N,
-                      out + (size_t)blockIdx.x * 5, redu, reds);
+                      out + (size_t)blockIdx.x * 5, share);
 }
 
 // N <= 32: one wavefront per GLCM, four per workgroup.
