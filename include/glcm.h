@@ -95,7 +95,13 @@ enum glcm_status {
 
 typedef struct glcm_plan_s *glcm_plan_t;
 
-/* Launch parameters of a plan, readable and (for tuning) overridable. */
+/* Launch parameters of a plan, readable and (for tuning) overridable.  They name
+ * an LDS kernel.  A slab- or strip-kernel plan whose parameters were neither set
+ * nor changed by the autotuner counts N <= 16 with offsets of 1, 2 or 4 pixels
+ * along the four directions on the matrix cores where that is the faster kernel
+ * (small and medium images, larger ones with most of a distance's offsets);
+ * setting any parameter but tile_rows to another value, or a force flag, makes
+ * the named kernel run.  The counts are the same. */
 typedef struct glcm_tuning {
     int replicas;       /* R: LDS copies of each GLCM per workgroup (power of two) */
     int wg_size;        /* threads per workgroup: 256, 512 or 1024 (the strip kernel runs
@@ -463,6 +469,9 @@ GLCM_API int glcm_batch_destroy(glcm_batch_t batch);
  * Layout of the batch kernel, chosen per plan.  The paper tunes the number of
  * GLCM copies per block and the block size by measurement (Section II.A,
  * Table III, Eq. (4)-(6)); the batch engine does the same for its own layout.
+ * With nothing set (all 0), N <= 16, offsets of 1 or 2 pixels along the four
+ * directions and images at most 2^19 pixels wide, the batch is counted on the
+ * matrix cores, without LDS copies; any value set asks for the LDS kernel.
  *
  *   replicas  LDS copies (dwords) of every bin: 4, 8 or 16; 0 = the default
  *             rule (the most that leave room for two workgroups per CU).
@@ -488,8 +497,8 @@ typedef struct glcm_batch_tuning {
 GLCM_API int glcm_batch_tuning(glcm_plan_t plan, glcm_batch_tuning_t *tuning, int set);
 
 /*
- * Times every batch layout that fits (wg_size 256, 512 x replicas 4, 8, 16 x
- * min_rows 4, 8, 16, 32) on the given images, `repeats` runs each after one warm-up run, with the
+ * Times the default and every batch layout that fits (wg_size 256, 512 x
+ * replicas 4, 8, 16 x min_rows 4, 8, 16, 32) on the given images, `repeats` runs each after one warm-up run, with the
  * statistics computed, and keeps the fastest in the plan for later batch calls
  * (glcm_batch_compute, glcm_batch_prepare).  tiles, T, lo, hi as for
  * glcm_batch_compute; repeats 1 .. 1000.  Allocates its own outputs and stream

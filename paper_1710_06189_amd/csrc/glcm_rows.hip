@@ -31,9 +31,9 @@ namespace {
 // come, 5 more of bank conflicts, whatever the vector instructions next to it
 // (4.1 a vote; with 4.8 and 5.8 the 8192^2 image took the same time).  Measured
 // on MI355X (slabs of four rows read with their halo, before, and this walk):
-// 8192^2 u16 band, N = 64, 12 offsets 233 to 224 us; 2937 x 3015 u8 crop, 7
-// offsets, N = 16 noise 24.8 to 21.9, N = 64 smooth 30.5 to 29.7.  Four rows at
-// a time instead of two: 259, 23.0, 33.8 (registers).
+// 8192^2 u16 band, N = 64, 12 offsets 233 to 224 us; u8 crops, 7 offsets: 2937 x
+// 3015 noise, N = 16, 24.8 to 21.9, 1531 x 1489 smooth, N = 64, 30.5 to 29.7.
+// Four rows at a time instead of two: 259, 23.0, 33.8 (registers).
 // ---------------------------------------------------------------------------
 struct Ring {
   uint32_t w[6];  // [left halo (4 px) | 16 px chunk | right halo (4 px)], one level per byte
