@@ -323,26 +323,29 @@ __device__ __forceinline__ double neg_plogp(double p, const LogPoint* t) { retur
 //
 // Only f1 and f9 need the bins one by one.  The others follow from the exact
 // integer marginals px, py and the distributions pd of |i - j| and ps of i + j:
-// f2 = sum d^2 pd, f5 = sum pd / (1 + d^2), cov = (var x + var y + (mean x -
-// mean y)^2 - f2) / 2, and since sum_j p(i, j) = px(i),
+// f2 = sum d^2 pd, f5 = sum pd / (1 + d^2), and since sum_j p(i, j) = px(i),
 //     HXY1 = -sum p ln(px py) = HX + HY,  HXY2 = -sum px py ln(px py) = HX + HY.
+// With a marginal on a single level p = px py, so f12 and f13 are 0 (and f3 is
+// 1 by definition).
+// The covariance is never taken as a difference of second moments in floating
+// point: where the two marginals lie apart those are near N^2 and cancel (4e9
+// counts in a corner left f3 at 0.20 instead of 0.289).
 // ---------------------------------------------------------------------------
 struct Moments {
   double asm_, ent;            // over the bins
-  double mux, vx, hx, muy, vy, hy;
-  double da, vd, hd, contrast, idm;  // of |i - j|
+  double cov, vx, hx, vy, hy;  // all three of cov, vx, vy times the same factor, or none
+  double contrast, idm, vd, hd;  // of |i - j|
   double sa, vs, hs;           // of i + j
-  double one;                  // non-zero: a marginal occupies a single level
+  bool one;                    // a marginal occupies a single level
 };
 
-__device__ __forceinline__ void haralick_store(const Moments& s, float* f) {
-  const double cov = 0.5 * (s.vx + s.vy + (s.mux - s.muy) * (s.mux - s.muy) - s.contrast);
+__device__ __forceinline__ void haralick_store(const Moments& s, double var_x, float* f) {
   const double hxy = s.hx + s.hy, hmax = s.hx > s.hy ? s.hx : s.hy;
   const double x = 1.0 - exp(-2.0 * (hxy - s.ent));
   f[0] = (float)s.asm_;
   f[1] = (float)s.contrast;
-  f[2] = (float)(s.one != 0.0 ? 1.0 : cov / sqrt(s.vx * s.vy));
-  f[3] = (float)s.vx;
+  f[2] = (float)(s.one ? 1.0 : s.cov / sqrt(s.vx * s.vy));
+  f[3] = (float)var_x;
   f[4] = (float)s.idm;
   f[5] = (float)s.sa;
   f[6] = (float)s.vs;
@@ -350,8 +353,49 @@ __device__ __forceinline__ void haralick_store(const Moments& s, float* f) {
   f[8] = (float)s.ent;
   f[9] = (float)s.vd;
   f[10] = (float)s.hd;
-  f[11] = (float)(hmax > 0.0 ? (s.ent - hxy) / hmax : 0.0);
-  f[12] = (float)sqrt(x > 0.0 ? x : 0.0);
+  f[11] = (float)(s.one ? 0.0 : (s.ent - hxy) / hmax);
+  f[12] = (float)sqrt(!s.one && x > 0.0 ? x : 0.0);
+}
+
+// a b - c d with about one rounding (Kahan): the products' rounding errors are
+// taken back exactly.  (Not contracted: p - q has to be the rounded products'.)
+__device__ __forceinline__ double difference_of_products(double a, double b, double c, double d) {
+#pragma clang fp contract(off)
+  const double p = a * b, q = c * d;
+  return (p - q) + (fma(a, b, -p) - fma(c, d, -q));
+}
+
+// What a wavefront keeps of a matrix of N <= 32: sums over the counts (not the
+// probabilities) of i, i^2, j, ... are whole numbers below 2^53 (T < 2^42), so
+// they are exact, and so is sum i j c = (sum i^2 c + sum j^2 c - sum (i - j)^2 c)
+// / 2; T^2 times a variance or the covariance then has one rounding.
+struct WholeMoments {
+  double T, asm_, ent;
+  double x1, x2, hx, y1, y2, hy;  // rows, columns: first and second sum, entropy
+  double d1, d2, hd, idm;         // |i - j|
+  double s1, s2, hs;              // i + j - (N - 1): below N in magnitude
+  double one;
+};
+
+__device__ __forceinline__ void haralick_store(const WholeMoments& w, double N, float* f) {
+  const double T = w.T, inv2 = 1.0 / (T * T);
+  Moments s;
+  s.asm_ = w.asm_;
+  s.ent = w.ent;
+  s.vx = difference_of_products(T, w.x2, w.x1, w.x1);
+  s.vy = difference_of_products(T, w.y2, w.y1, w.y1);
+  s.cov = difference_of_products(T, 0.5 * (w.x2 + w.y2 - w.d2), w.x1, w.y1);
+  s.hx = w.hx;
+  s.hy = w.hy;
+  s.contrast = w.d2 / T;
+  s.idm = w.idm;
+  s.vd = difference_of_products(T, w.d2, w.d1, w.d1) * inv2;
+  s.hd = w.hd;
+  s.sa = (w.s1 + (N - 1.0) * T) / T;
+  s.vs = difference_of_products(T, w.s2, w.s1, w.s1) * inv2;
+  s.hs = w.hs;
+  s.one = w.one != 0.0;
+  haralick_store(s, s.vx * inv2, f);
 }
 
 // Sum over a group of L lanes (16 or 32), on all of them.
@@ -380,12 +424,12 @@ template <int L, bool VEC>
 __global__ __launch_bounds__(kStatsThreads, L == 16 ? 4 : 3) void k_haralick_wave(StatsArgs a) {
   __shared__ LogPoint table[kLogPoints];
   __shared__ uint32_t tiles[kStatsWaves][L * (L + 1)];
-  __shared__ Moments parked[kStatsWaves][kPark];
+  __shared__ WholeMoments parked[kStatsWaves][kPark];
   const uint32_t N = (uint32_t)a.N, NN = N * N, pitch = lds_pitch(N);
   const int lane = threadIdx.x & 63;
   const uint32_t l = (uint32_t)lane & (L - 1u);
   uint32_t* M = tiles[threadIdx.x >> 6];
-  Moments* park = parked[threadIdx.x >> 6];
+  WholeMoments* park = parked[threadIdx.x >> 6];
   const double dl = (double)l, idm_w = 1.0 / (1.0 + dl * dl);
   log_table(table);
   __syncthreads();
@@ -404,7 +448,7 @@ __global__ __launch_bounds__(kStatsThreads, L == 16 ? 4 : 3) void k_haralick_wav
     }
     T = wave_sum(T);
     if (held == 0) k_first = k;
-    Moments* st = park + held;
+    WholeMoments* st = park + held;
     if (T == 0.0) {
       if (lane == 0) st->asm_ = -1.0;  // empty: zeros
     } else {
@@ -431,39 +475,38 @@ __global__ __launch_bounds__(kStatsThreads, L == 16 ? 4 : 3) void k_haralick_wav
           }
         }
         if (wrap_at >= N) before = sum;
-        // x0: the entry of value l; x1: that of value l + N (i + j only).  The
+        // c0: the count of value l; c1: that of value l + N (i + j only).  The
         // wrapped part of |i - j| class d counts for N - d.
         const uint64_t after = sum - before;
-        double x0 = (double)before, x1 = task == 3 ? (double)after : 0.0;
+        double c0 = (double)before;
+        const double c1 = task == 3 ? (double)after : 0.0;
         const int from = (int)(((uint32_t)lane & ~(L - 1u)) + (l ? N - l : 0u));  // lane of class N - l
         const double folded = __shfl((double)after, from & 63);
-        if (task == 2 && l != 0 && l < N) x0 += folded;
-        x0 = quotient(x0, T, inv);
-        x1 = quotient(x1, T, inv);
-        const double v1 = dl + (double)N;
-        const double mean = group_sum<L>(dl * x0 + v1 * x1);
-        const double d0 = dl - mean, d1 = v1 - mean;
-        const double var = group_sum<L>(d0 * d0 * x0 + d1 * d1 * x1);
+        if (task == 2 && l != 0 && l < N) c0 += folded;
+        const double v0 = task == 3 ? dl - (double)(N - 1u) : dl, v1 = dl + 1.0;
+        const double a0 = v0 * c0, a1 = v1 * c1;
+        const double m1 = group_sum<L>(a0 + a1), m2 = group_sum<L>(fma(v0, a0, v1 * a1));
+        const double x0 = quotient(c0, T, inv), x1 = quotient(c1, T, inv);
         const double ent = group_sum<L>(neg_plogp(x0, table) + neg_plogp(x1, table));
-        const uint64_t live = __ballot(x0 > 0.0);
+        const uint64_t live = __ballot(c0 > 0.0);
         if (L == 16 || pass == 1) {
-          const double con = group_sum<L>(dl * dl * x0), idm = group_sum<L>(idm_w * x0);
+          const double idm = group_sum<L>(idm_w * x0);
           if (l == 0 && task == 2) {
-            st->da = mean; st->vd = var; st->hd = ent; st->contrast = con; st->idm = idm;
+            st->d1 = m1; st->d2 = m2; st->hd = ent; st->idm = idm;
           }
           if (l == 0 && task == 3) {
-            st->sa = mean; st->vs = var; st->hs = ent;
+            st->s1 = m1; st->s2 = m2; st->hs = ent;
           }
         }
         if (L == 16 || pass == 0) {
           const uint32_t rows = (uint32_t)(L == 16 ? live & 0xffffu : live & 0xffffffffu);
           const uint32_t cols = (uint32_t)(L == 16 ? (live >> 16) & 0xffffu : live >> 32);
           if (l == 0 && task == 0) {
-            st->mux = mean; st->vx = var; st->hx = ent;
+            st->x1 = m1; st->x2 = m2; st->hx = ent;
             st->one = __popc(rows) == 1 || __popc(cols) == 1 ? 1.0 : 0.0;
           }
           if (l == 0 && task == 1) {
-            st->muy = mean; st->vy = var; st->hy = ent;
+            st->y1 = m1; st->y2 = m2; st->hy = ent;
           }
         }
       }
@@ -478,6 +521,7 @@ __global__ __launch_bounds__(kStatsThreads, L == 16 ? 4 : 3) void k_haralick_wav
       sq = wave_sum(sq);
       ent = wave_sum(ent);
       if (lane == 0) {
+        st->T = T;
         st->asm_ = sq;
         st->ent = ent;
       }
@@ -486,11 +530,11 @@ __global__ __launch_bounds__(kStatsThreads, L == 16 ? 4 : 3) void k_haralick_wav
       wave_sync_lds();
       if (lane < held) {
         float* f = a.out_f + (size_t)(k_first + lane * nwaves) * kHaralickStats;
-        const Moments s = park[lane];
+        const WholeMoments s = park[lane];
         if (s.asm_ < 0.0) {
           for (int q = 0; q < kHaralickStats; ++q) f[q] = 0.0f;
         } else {
-          haralick_store(s, f);
+          haralick_store(s, (double)N, f);
         }
       }
       wave_sync_lds();
@@ -510,9 +554,13 @@ __global__ __launch_bounds__(kStatsThreads, L == 16 ? 4 : 3) void k_haralick_wav
 // a thread per diagonal and three logarithm terms a bin).
 template <int W, typename C>
 __device__ __forceinline__ void haralick_bins(const uint32_t* P, int N, double T, double inv, C* ps, C* pd,
-                                              const LogPoint* table, double& sq, double& ent) {
+                                              const LogPoint* table, double mux, double muy, double& sq, double& ent,
+                                              double& cov) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (int j0 = 0; j0 < N; j0 += 256) {
+    double dj[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) dj[e] = (double)(j0 + 64 * e + lane) - muy;
     uint32_t next[4];
     auto load = [&](int i) {
 #pragma unroll
@@ -528,6 +576,7 @@ __device__ __forceinline__ void haralick_bins(const uint32_t* P, int N, double T
 #pragma unroll
       for (int e = 0; e < 4; ++e) c[e] = next[e];
       load(i + W);
+      double along = 0.0;  // sum of (j - muy) p along the row
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int j = j0 + 64 * e + lane;
@@ -538,8 +587,10 @@ __device__ __forceinline__ void haralick_bins(const uint32_t* P, int N, double T
           p = fma(fma(-p, T, (double)c[e]), inv, p);
           sq += p * p;
           ent -= p * log_tab(p, table);
+          along = fma(p, dj[e], along);
         }
       }
+      cov = fma((double)i - mux, along, cov);
     }
   }
 }
@@ -548,7 +599,7 @@ template <int W>
 __global__ __launch_bounds__(64 * W) void k_haralick(StatsArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];
   __shared__ LogPoint table[kLogPoints];
-  __shared__ double part[W], part2[W], sums[W][6];
+  __shared__ double part[W], part2[W], part3[W], sums[W][5];
   __shared__ int occupied[W];
   const int N = a.N, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   // row[N] col[N] as doubles, then ps[2N - 1] pd[N] as 64- or 32-bit counts
@@ -599,17 +650,27 @@ __global__ __launch_bounds__(64 * W) void k_haralick(StatsArgs a) {
     }
     const double inv = 1.0 / T;
     const bool narrow = T <= 4294967295.0;
-    double sq = 0.0, ent = 0.0;
+    // the marginals' means, by every wavefront (the covariance is summed about them)
+    double mux = 0.0, muy = 0.0;
+    for (int t = lane; t < N; t += 64) {
+      mux = fma((double)t, row[t], mux);
+      muy = fma((double)t, col[t], muy);
+    }
+    mux = wave_sum(mux) * inv;
+    muy = wave_sum(muy) * inv;
+    double sq = 0.0, ent = 0.0, cov = 0.0;
     if (narrow)
-      haralick_bins<W, uint32_t>(P, N, T, inv, ps32, pd32, table, sq, ent);
+      haralick_bins<W, uint32_t>(P, N, T, inv, ps32, pd32, table, mux, muy, sq, ent, cov);
     else
-      haralick_bins<W, unsigned long long>(P, N, T, inv, ps, pd, table, sq, ent);
+      haralick_bins<W, unsigned long long>(P, N, T, inv, ps, pd, table, mux, muy, sq, ent, cov);
     sq = wave_sum(sq);
     ent = wave_sum(ent);
+    cov = wave_sum(cov);
     __syncthreads();
     if (lane == 0) {
       part[wave] = sq;
       part2[wave] = ent;
+      part3[wave] = cov;
     }
     // distribution `task` (0 rows, 1 columns, 2 |i - j|, 3 i + j) by W / 4 wavefronts
     constexpr int G = W / 4;
@@ -658,22 +719,23 @@ __global__ __launch_bounds__(64 * W) void k_haralick(StatsArgs a) {
       };
       int ox = 0, oy = 0;
       Moments s;
-      s.asm_ = s.ent = 0.0;
+      s.asm_ = s.ent = s.cov = 0.0;
       for (int w = 0; w < W; ++w) {
         s.asm_ += part[w];
         s.ent += part2[w];
+        s.cov += part3[w];
       }
       for (int w = 0; w < G; ++w) {
         ox += occupied[w];
         oy += occupied[G + w];
       }
-      s.mux = over(0, 0); s.hx = over(0, 1); s.vx = over(0, 4);
-      s.muy = over(1, 0); s.hy = over(1, 1); s.vy = over(1, 4);
-      s.da = over(2, 0); s.hd = over(2, 1); s.vd = over(2, 4);
+      s.hx = over(0, 1); s.vx = over(0, 4);
+      s.hy = over(1, 1); s.vy = over(1, 4);
+      s.hd = over(2, 1); s.vd = over(2, 4);
       s.contrast = over(2, 2); s.idm = over(2, 3);
       s.sa = over(3, 0); s.hs = over(3, 1); s.vs = over(3, 4);
-      s.one = ox == 1 || oy == 1 ? 1.0 : 0.0;
-      haralick_store(s, f);
+      s.one = ox == 1 || oy == 1;
+      haralick_store(s, s.vx, f);
     }
   }
 }
