@@ -207,8 +207,8 @@ struct glcm_plan_s {
   uint32_t* xbuf = nullptr;  // [kXcdSlots][K*N*N] accumulation slices, kept zero between calls
   uint32_t xslots = glcm::kXcdSlots;  // slices the device's XCC_IDs reach (the rest stay zero)
   bool no_alloc = false;  // a transient plan of compute_in_workspace: never allocate (no staging copy)
-  size_t partials_cap = SIZE_MAX;  // most bytes of partials the plan may hold (glcm::limit_partials)
-
+  glcm::LevelStore levels;         // the level-slice kernel's partials
+  size_t levels_most = SIZE_MAX;   // most bytes the plan may take for them (glcm::limit_levels)
 
   // ordering across streams
   hipEvent_t done = nullptr;
@@ -419,35 +419,8 @@ bool levels_plan(const glcm_plan_s* p) {
          t.replicas == 1 && t.merge == 0 && p->xbuf != nullptr;
 }
 
-// Layout of the level-slice kernel for rows [y_begin, y_end) of a W x H image:
-// slices of whole rows of a GLCM of `levels` levels that fit the LDS, and bands
-// so that the workgroups fill the CUs once, each with at least two steps of
-// pairs.
-struct LevelLayout {
-  int slices = 1, bands = 1;
-  uint32_t slice_rows = 0, slice_dwords = 0, spill_cap = 0;
-  uint64_t units = 0, row_words = 0;  // (offset, slice) pairs; words of partials a workgroup owns
-  uint64_t bytes() const { return units * (uint64_t)bands * row_words * 4u; }
-};
-
-LevelLayout level_layout(const glcm_plan_s* p, int levels, int W, int rows) {
-  LevelLayout L;
-  const uint64_t N = (uint64_t)levels, pitch = glcm::level_pitch((uint32_t)levels);
-  const uint64_t most = (uint64_t)p->lds_budget_words / pitch;  // levels per slice
-  const uint64_t S0 = (N + most - 1) / most;
-  L.slice_rows = (uint32_t)((N + S0 - 1) / S0);
-  L.slices = (int)((N + L.slice_rows - 1) / L.slice_rows);
-  L.slice_dwords = (uint32_t)(((uint64_t)L.slice_rows * pitch + 3) & ~3ull);
-  L.units = (uint64_t)p->K * (uint64_t)L.slices;
-  const uint64_t chunks = (((uint64_t)W + 15) / 16) * (uint64_t)rows;
-  const uint64_t per_cu = std::max<uint64_t>(1, std::min<uint64_t>(2, (uint64_t)p->lds_budget_words / L.slice_dwords));
-  uint64_t bands = std::max<uint64_t>(1, (uint64_t)std::max(1, p->num_cus) * per_cu / L.units);
-  bands = std::min(bands, std::max<uint64_t>(1, chunks / (2 * glcm::kLevelThreads)));
-  L.bands = (int)bands;
-  // a spill takes 2^15 of a workgroup's pairs (at most 16 per chunk)
-  L.spill_cap = (uint32_t)((chunks / bands + 1) * 16 / 32768 + 1);
-  L.row_words = (uint64_t)L.slice_dwords + 1 + L.spill_cap;
-  return L;
+glcm::LevelLayout level_layout(const glcm_plan_s* p, int levels, int W, int rows) {
+  return glcm::level_layout(levels, p->K, W, rows, p->lds_budget_words, p->num_cus);
 }
 
 // The matrix-core kernel (glcm_onehot.hip): up to 16 levels, every offset along
@@ -690,6 +663,7 @@ void plan_release(glcm_plan_t p) {
   }
   if (p->copy_stream) (void)hipStreamDestroy(p->copy_stream);
   if (p->partials) (void)hipFree(p->partials);
+  if (p->levels.mem) (void)hipFree(p->levels.mem);
   if (p->stage) (void)hipFree(p->stage);
   if (p->xbuf) (void)hipFree(p->xbuf);
   if (p->batch_pending) (void)hipEventSynchronize(p->batch_uploaded);
@@ -743,20 +717,26 @@ int record_done(glcm_plan_t p, hipStream_t s) {
   return GLCM_OK;
 }
 
-// Makes room for the level-slice kernel's partials (bytes for this call):
-// false when the plan may not hold them, or would have to allocate while
-// `stream` is being captured; *rc is then GLCM_OK, or the HIP failure.
-bool level_partials(glcm_plan_t p, size_t bytes, hipStream_t stream, int* rc) {
-  *rc = GLCM_OK;
-  if (bytes <= p->partials_bytes) return true;
-  if (bytes > p->partials_cap) return false;
+// Whether the plan has its partials for the level-slice kernel, making them if
+// that is allowed: not while `stream` is being captured (nullptr: a plan being
+// created, no stream), not beyond levels_most, and not a failure where the
+// memory cannot be had.
+bool hold_levels(glcm_plan_t p, const hipStream_t* stream) {
+  if (p->levels.mem) return true;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
+  if (stream && hipStreamIsCapturing(*stream, &cs) != hipSuccess) {
     (void)hipGetLastError();
-    return false;
+    cs = hipStreamCaptureStatusActive;
   }
-  *rc = ensure_partials(p, bytes);
-  return *rc == GLCM_OK;
+  const uint64_t want = glcm::level_reserve(p->N, p->k_cap, p->max_W, p->max_H, p->lds_budget_words, p->num_cus);
+  return p->levels.hold(want, p->levels_most, cs == hipStreamCaptureStatusNone, [](size_t bytes) -> void* {
+    void* mem = nullptr;
+    if (hipMalloc(&mem, bytes) != hipSuccess) {
+      (void)hipGetLastError();
+      return nullptr;
+    }
+    return mem;
+  });
 }
 
 // Counts rows [y_begin, y_end) with the level-slice kernel into out.
@@ -768,9 +748,9 @@ int count_levels(glcm_plan_t p, const VoteArgs& v, int b, uint32_t* out, bool ac
   // only where no pixel lies above hi (its level, N - 1, has no value)
   const uint32_t values = v.q.hi - v.q.lo + 1u, top = b == 1 ? 255u : 65535u;
   uint32_t counted = (uint32_t)p->N;
-  LevelLayout L = level_layout(p, p->N, v.W, v.y_end - v.y_begin);
+  glcm::LevelLayout L = level_layout(p, p->N, v.W, v.y_end - v.y_begin);
   if (values < counted && v.q.hi == top) {
-    const LevelLayout by_value = level_layout(p, (int)values, v.W, v.y_end - v.y_begin);
+    const glcm::LevelLayout by_value = level_layout(p, (int)values, v.W, v.y_end - v.y_begin);
     if (by_value.slices == 1) {
       L = by_value;
       counted = values;
@@ -780,20 +760,11 @@ int count_levels(glcm_plan_t p, const VoteArgs& v, int b, uint32_t* out, bool ac
   if (p->no_alloc) {
     // the caller's accumulation slices serve as partials (no other kernel of
     // this call uses them)
-    const uint64_t room = (uint64_t)glcm::kXcdSlots * v.words_total * 4u;
-    if (L.bytes() > room) L.bands = (int)std::max<uint64_t>(1, room / (L.bytes() / (uint64_t)L.bands));
-    const uint64_t chunks = (((uint64_t)v.W + 15) / 16) * (uint64_t)(v.y_end - v.y_begin);
-    for (; L.bands >= 1; --L.bands) {  // fewer bands have longer spill lists
-      L.spill_cap = (uint32_t)((chunks / (uint64_t)L.bands + 1) * 16 / 32768 + 1);
-      L.row_words = (uint64_t)L.slice_dwords + 1 + L.spill_cap;
-      if (L.bytes() <= room) break;
-    }
-    if (L.bands < 1) return GLCM_OK;
+    if (!L.fit((uint64_t)glcm::kXcdSlots * v.words_total * 4u)) return GLCM_OK;
     mem = p->xbuf;
   } else {
-    int rc = GLCM_OK;
-    if (!level_partials(p, (size_t)L.bytes(), stream, &rc)) return rc;
-    mem = p->partials;
+    if (!hold_levels(p, &stream) || !L.fit(p->levels.bytes)) return GLCM_OK;
+    mem = p->levels.mem;
   }
   glcm::LevelArgs a;
   std::memset(&a, 0, sizeof(a));
@@ -1293,7 +1264,7 @@ int count_host(glcm_plan_t p, const void* img, bool pinned, int W, int H, int64_
 }
 
 size_t plan_device_bytes(const glcm_plan_s* p) {
-  size_t b = p->partials_bytes + p->batch_cap + p->stage_bytes;
+  size_t b = p->partials_bytes + p->levels.bytes + p->batch_cap + p->stage_bytes;
   if (p->xbuf) b += (size_t)glcm::kXcdSlots * (size_t)p->k_cap * p->N * p->N * 4u;
   for (int s = 0; s < glcm_plan_s::kSlots; ++s)
     if (p->dev_tile[s]) b += p->tile_bytes;
@@ -1478,9 +1449,9 @@ int create_plan(glcm_plan_t* plan, int dtype, int N, int K, const glcm_offset_t*
   return GLCM_OK;
 }
 
-void limit_partials(glcm_plan_t plan, size_t more_bytes) {
+void limit_levels(glcm_plan_t plan, size_t most_bytes) {
   std::lock_guard<std::mutex> lk(plan->mu);
-  plan->partials_cap = more_bytes > SIZE_MAX - plan->partials_bytes ? SIZE_MAX : plan->partials_bytes + more_bytes;
+  plan->levels_most = most_bytes;
 }
 
 }  // namespace glcm
@@ -1490,20 +1461,10 @@ GLCM_API int glcm_plan_create(glcm_plan_t* plan, int dtype, int N, int K, const 
                      int max_H, uint32_t flags) {
   int rc = glcm::create_plan(plan, dtype, N, K, offsets, max_W, max_H, flags);
   if (rc != GLCM_OK || !levels_plan(*plan)) return rc;
-  // the partials of the largest image, so that no call allocates them (also
-  // enough for fewer offsets: the workgroups of a call fill the CUs at most
-  // once unless K alone is more)
-  const LevelLayout L = level_layout(*plan, N, max_W, max_H);
-  const uint64_t per_cu = std::max<uint64_t>(1, std::min<uint64_t>(2, (uint64_t)(*plan)->lds_budget_words / L.slice_dwords));
-  const uint64_t groups = std::max<uint64_t>(L.units * (uint64_t)L.bands,
-                                             std::min<uint64_t>((uint64_t)(*plan)->num_cus * per_cu,
-                                                                L.units * (uint64_t)L.bands * 2));
-  rc = ensure_partials(*plan, (size_t)(groups * L.row_words * 4u));
-  if (rc != GLCM_OK) {
-    (void)glcm_plan_destroy(*plan);
-    *plan = nullptr;
-  }
-  return rc;
+  if (hold_levels(*plan, nullptr)) return GLCM_OK;  // now, so that no call allocates them
+  (void)glcm_plan_destroy(*plan);
+  *plan = nullptr;
+  return GLCM_ENOMEM;
 }
 
 GLCM_API int glcm_plan_tuning(glcm_plan_t plan, glcm_tuning_t* tuning, int set) {

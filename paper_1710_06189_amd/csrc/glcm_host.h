@@ -32,14 +32,14 @@ int compute_in_workspace(uint32_t* slices, size_t slice_words, const void* img, 
                          int dtype, int N, uint32_t lo, uint32_t hi, const glcm_offset_t* offsets, int K,
                          uint32_t* out, hipStream_t stream);
 
-// glcm_plan_create without the level-slice kernel's partials: calls that need
-// them allocate them, up to what limit_partials leaves.
+// glcm_plan_create without the level-slice kernel's partials: the first call
+// that needs them allocates them, once, within what limit_levels leaves.
 int create_plan(glcm_plan_t* plan, int dtype, int N, int K, const glcm_offset_t* offsets, int max_W, int max_H,
                 uint32_t flags);
 
-// The plan may add at most more_bytes to the partials it holds; a call that
-// would need more takes the kernel without them.
-void limit_partials(glcm_plan_t plan, size_t more_bytes);
+// The plan may take at most most_bytes for the level-slice kernel's partials if
+// it has none yet; without them its calls take the kernel that needs none.
+void limit_levels(glcm_plan_t plan, size_t most_bytes);
 
 // glcm_batch_compute with a destination per image: image t's counts go to
 // outs[t] (device, K*N*N words) and its statistics to feats[t] (K*5 floats;

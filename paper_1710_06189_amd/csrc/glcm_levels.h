@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstddef>
 #include <cstdint>
 
 #include "glcm_internal.h"
@@ -82,6 +83,91 @@ __host__ __device__ inline LevelChunk level_chunk(const LevelRect& r, int c) {
 // An odd pitch: neighbouring levels of smooth images (b near a) then fall on
 // banks that move with a as well as with b.
 constexpr uint32_t level_pitch(uint32_t N) { return ((N + 1u) / 2u) | 1u; }
+
+// Layout for `rows` first-pixel rows of width W of an image of `levels` levels
+// and K offsets: slices of whole rows of a GLCM that fit the LDS (lds_words), and
+// bands so that the workgroups fill the CUs once, each with at least two steps
+// of pairs.
+struct LevelLayout {
+  int slices = 1, bands = 1;
+  uint32_t slice_rows = 0, slice_dwords = 0, spill_cap = 0;
+  uint64_t chunks = 0;
+  uint64_t units = 0, row_words = 0;  // (offset, slice) pairs; words of partials a workgroup owns
+  uint64_t bytes() const { return units * (uint64_t)bands * row_words * 4u; }
+  // workgroups a CU holds
+  uint64_t per_cu(uint64_t lds_words) const {
+    return std::max<uint64_t>(1, std::min<uint64_t>(2, lds_words / slice_dwords));
+  }
+  void set_bands(int b) {
+    bands = b;
+    // a spill takes 2^15 of a workgroup's pairs (at most 16 per chunk)
+    spill_cap = (uint32_t)((chunks / (uint64_t)b + 1) * 16 / 32768 + 1);
+    row_words = (uint64_t)slice_dwords + 1 + spill_cap;
+  }
+  // As many of the bands as `room` bytes hold; false if not even one does.
+  bool fit(uint64_t room) {
+    int b = bands;
+    if (bytes() > room) b = (int)std::max<uint64_t>(1, room / (bytes() / (uint64_t)b));
+    for (; b >= 1; --b) {  // (fewer bands have longer spill lists)
+      set_bands(b);
+      if (bytes() <= room) return true;
+    }
+    return false;
+  }
+};
+
+inline LevelLayout level_layout(int levels, int K, int W, int rows, int lds_words, int cus) {
+  LevelLayout L;
+  const uint64_t N = (uint64_t)levels, pitch = level_pitch((uint32_t)levels);
+  const uint64_t most = (uint64_t)lds_words / pitch;  // levels per slice
+  const uint64_t S0 = (N + most - 1) / most;
+  L.slice_rows = (uint32_t)((N + S0 - 1) / S0);
+  L.slices = (int)((N + L.slice_rows - 1) / L.slice_rows);
+  L.slice_dwords = (uint32_t)(((uint64_t)L.slice_rows * pitch + 3) & ~3ull);
+  L.units = (uint64_t)K * (uint64_t)L.slices;
+  L.chunks = (((uint64_t)W + 15) / 16) * (uint64_t)rows;
+  const uint64_t fill = std::max<uint64_t>(1, (uint64_t)std::max(1, cus) * L.per_cu((uint64_t)lds_words) / L.units);
+  L.set_bands((int)std::min(fill, std::max<uint64_t>(1, L.chunks / (2 * kLevelThreads))));
+  return L;
+}
+
+// Bytes of partials that hold every call of a plan of N levels, at most K
+// offsets and images up to W x H: counted by level, and by value for every
+// number of values below N whose GLCM is one slice (a workgroup fewer or more a
+// CU, so often more bytes than by level: N = 300, one offset, 4096^2: 33.8
+// against 23.2 MB).
+inline uint64_t level_reserve(int N, int K, int W, int H, int lds_words, int cus) {
+  uint64_t most = 0;
+  for (int levels = N; levels >= 1; --levels) {
+    const LevelLayout L = level_layout(levels, K, W, H, lds_words, cus);
+    if (levels < N && L.slices != 1) continue;
+    // workgroups and entries of their spill lists, whatever the offsets and rows of a call
+    const uint64_t groups = std::min(std::max(L.units, (uint64_t)std::max(1, cus) * L.per_cu((uint64_t)lds_words)),
+                                     L.units * std::max<uint64_t>(1, L.chunks / (2 * kLevelThreads)));
+    const uint64_t spills = L.units * (L.chunks / 2048 + 1) + 2 * groups;
+    most = std::max(most, (groups * ((uint64_t)L.slice_dwords + 1) + spills) * 4u);
+  }
+  return most;
+}
+
+// A plan's partials of the level-slice kernel.  Made once, for every call the
+// plan can get, and neither moved nor freed before the plan is: a captured
+// graph keeps the pointer.  Without it (not allowed, no memory left) the plan
+// counts with ranges of 32-bit bins, which need none.
+struct LevelStore {
+  uint32_t* mem = nullptr;
+  size_t bytes = 0;
+  // true when the store exists, or `make` (bytes -> pointer or null) could be
+  // asked for it and gave it
+  template <class Make>
+  bool hold(uint64_t want, uint64_t most, bool may_allocate, Make make) {
+    if (mem) return true;
+    if (!may_allocate || want > most) return false;
+    mem = (uint32_t*)make((size_t)want);
+    if (mem) bytes = (size_t)want;
+    return mem != nullptr;
+  }
+};
 
 hipError_t launch_vote_levels(const LevelArgs& a, int dtype_bytes, hipStream_t stream, const LaunchTiming& tm = {});
 

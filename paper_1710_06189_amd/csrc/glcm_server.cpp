@@ -396,7 +396,7 @@ int launch(glcm_server_s* s, Admission& a) {
     // what the call may allocate beside what is held (only this thread admits,
     // so nothing else takes it meanwhile)
     std::lock_guard<std::mutex> lk(s->mu);
-    glcm::limit_partials(plan, s->budget > s->held ? (size_t)(s->budget - s->held) : 0);
+    glcm::limit_levels(plan, s->budget > s->held ? (size_t)(s->budget - s->held) : 0);
   }
   // (the group is fixed once admitted: only this thread reads it until the
   // launch completes)
