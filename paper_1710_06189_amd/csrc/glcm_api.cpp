@@ -1461,10 +1461,8 @@ GLCM_API int glcm_plan_create(glcm_plan_t* plan, int dtype, int N, int K, const 
                      int max_H, uint32_t flags) {
   int rc = glcm::create_plan(plan, dtype, N, K, offsets, max_W, max_H, flags);
   if (rc != GLCM_OK || !levels_plan(*plan)) return rc;
-  if (hold_levels(*plan, nullptr)) return GLCM_OK;  // now, so that no call allocates them
-  (void)glcm_plan_destroy(*plan);
-  *plan = nullptr;
-  return GLCM_ENOMEM;
+  (void)hold_levels(*plan, nullptr);  // now, so that no call allocates them
+  return GLCM_OK;
 }
 
 GLCM_API int glcm_plan_tuning(glcm_plan_t plan, glcm_tuning_t* tuning, int set) {
