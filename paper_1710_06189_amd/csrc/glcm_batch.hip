@@ -173,7 +173,7 @@ __device__ __forceinline__ void batch_item(const BatchArgs& a, const BatchTile& 
   // one wavefront per GLCM (a wavefront takes several when the workgroup has
   // fewer wavefronts than K)
   for (int k = wave; k < K; k += (int)(blockDim.x >> 6))
-    glcm_features_any(merged + (uint32_t)k * NN, N, fdst + 5 * k);
+    glcm_features_any(merged + (uint32_t)k * NN, N, fdst + 5 * k, lane_id());
 }
 
 // Wavefronts a SIMD holds: as many as the counting loop's registers allow (the
@@ -313,7 +313,7 @@ __global__ __launch_bounds__(kBatchThreads, 4) void k_batch_onehot(BatchArgs a) 
       float* const fdst = a.outs ? (a.feats ? a.feats[t.index] : nullptr)
                                  : (a.feat ? a.feat + (size_t)t.index * K * 5 : nullptr);
       if (fdst && (!big || wave < K))
-        glcm_features_16(own + (big ? (uint32_t)wave * NN : 0u), N, big ? 1 : K, big, fdst + (big ? 5 * wave : 0));
+        glcm_features_16<true>(own + (big ? (uint32_t)wave * NN : 0u), N, big ? 1 : K, big, fdst + (big ? 5 * wave : 0), lane_id());
     }
     // thread 0's number, to all
     __syncthreads();
@@ -358,7 +358,7 @@ __global__ __launch_bounds__(kBatchThreads) void k_batch_fin(BatchArgs a) {
   __syncthreads();
   const int wave = (int)(threadIdx.x >> 6);
   for (int k = wave; k < a.K; k += (int)(blockDim.x >> 6))
-    glcm_features_any(lds + (uint32_t)k * N * N, N, fdst + 5 * k);
+    glcm_features_any(lds + (uint32_t)k * N * N, N, fdst + 5 * k, lane_id());
 }
 
 }  // namespace

@@ -357,14 +357,6 @@ __device__ __forceinline__ void haralick_store(const Moments& s, double var_x, f
   f[12] = (float)sqrt(!s.one && x > 0.0 ? x : 0.0);
 }
 
-// a b - c d with about one rounding (Kahan): the products' rounding errors are
-// taken back exactly.  (Not contracted: p - q has to be the rounded products'.)
-__device__ __forceinline__ double difference_of_products(double a, double b, double c, double d) {
-#pragma clang fp contract(off)
-  const double p = a * b, q = c * d;
-  return (p - q) + (fma(a, b, -p) - fma(c, d, -q));
-}
-
 // What a wavefront keeps of a matrix of N <= 32: sums over the counts (not the
 // probabilities) of i, i^2, j, ... are whole numbers below 2^53 (T < 2^42), so
 // they are exact, and so is sum i j c = (sum i^2 c + sum j^2 c - sum (i - j)^2 c)

@@ -80,5 +80,13 @@ __device__ __forceinline__ double quad_bcast(double v) {
   return dpp_move<Q * 0x55, 0xf>(v);
 }
 
+// a b - c d with about one rounding (Kahan): the products' rounding errors are
+// taken back exactly.  (Not contracted: p - q has to be the rounded products'.)
+__device__ __forceinline__ double difference_of_products(double a, double b, double c, double d) {
+#pragma clang fp contract(off)
+  const double p = a * b, q = c * d;
+  return (p - q) + (fma(a, b, -p) - fma(c, d, -q));
+}
+
 }  // namespace
 }  // namespace glcm
