@@ -106,6 +106,18 @@ __device__ __forceinline__ void batch_votes(const BatchArgs& a, const BatchTile&
   }
 }
 
+// The statistics of one GLCM at LDS address P, by one wavefront.  A call: inlined,
+// they made the counting loop hold 7 to 18 more registers and spill (121 to 139
+// of them at 8-bit pixels and a reach of 1, so 3 wavefronts a SIMD instead of 4, or
+// scratch where 4 were asked for; with the call 115).  Measured on MI355X, 3000
+// images of 32-512 px, us a batch without the statistics, inlined and held to 4
+// wavefronts; with the call: N = 24 407; 333, N = 36 (one offset) 152; 130, N = 16
+// with 8 copies and 256 threads 230; 197.
+typedef __attribute__((address_space(3))) uint32_t lds_u32;
+__device__ __attribute__((noinline)) void batch_features(uint32_t P, uint32_t N, float* o) {
+  glcm_features_any((const uint32_t*)(const lds_u32*)(size_t)P, N, o, lane_id());
+}
+
 // One item (an image or a band of one) into the workgroup's LDS copies,
 // which are zero on entry and zero again on return (the merge clears what it
 // reads, so the next item needs no clearing pass).
@@ -173,13 +185,8 @@ __device__ __forceinline__ void batch_item(const BatchArgs& a, const BatchTile& 
   // one wavefront per GLCM (a wavefront takes several when the workgroup has
   // fewer wavefronts than K)
   for (int k = wave; k < K; k += (int)(blockDim.x >> 6))
-    glcm_features_any(merged + (uint32_t)k * NN, N, fdst + 5 * k, lane_id());
+    batch_features(lds_address(merged) + 4u * (uint32_t)k * NN, N, fdst + 5 * k);
 }
-
-// Wavefronts a SIMD holds: as many as the counting loop's registers allow (the
-// statistics, inlined, would take 18 more; measured on MI355X, 4096 images of
-// 32-512 px, N = 16, d = 1, 512 threads with 16 copies: 188 us at 4, 283 at 3).
-constexpr int batch_waves(int pixel_bytes, int maxdy) { return 6 - pixel_bytes - maxdy; }
 
 // Persistent workgroups: each takes the next item from a counter (items are
 // ordered largest first) until none is left.  The counter is zero at launch.
@@ -187,7 +194,7 @@ constexpr int batch_waves(int pixel_bytes, int maxdy) { return 6 - pixel_bytes -
 // the counter ends at nitems + gridDim.x, and the workgroup that drew the
 // last number sets it back to zero: no other workgroup touches it after.
 template <typename Pix, int MAXDY, int D, int WG>
-__global__ __launch_bounds__(WG, batch_waves(sizeof(Pix), MAXDY)) void k_batch(BatchArgs a) {
+__global__ __launch_bounds__(WG) void k_batch(BatchArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
   __shared__ uint32_t s_item;
   const uint32_t vote_words = a.pitch * a.pitch * (uint32_t)a.K * D;
@@ -312,8 +319,13 @@ __global__ __launch_bounds__(kBatchThreads, 4) void k_batch_onehot(BatchArgs a) 
     if (have && !band) {
       float* const fdst = a.outs ? (a.feats ? a.feats[t.index] : nullptr)
                                  : (a.feat ? a.feat + (size_t)t.index * K * 5 : nullptr);
-      if (fdst && (!big || wave < K))
-        glcm_features_16<true>(own + (big ? (uint32_t)wave * NN : 0u), N, big ? 1 : K, big, fdst + (big ? 5 * wave : 0), lane_id());
+      if (fdst && (!big || wave < K)) {
+        // (opaque, or what the statistics derive from them is computed once, ahead
+        // of the loop over the items, and takes registers from the walk)
+        uint32_t n = N, ln = lane_id();
+        asm volatile("" : "+s"(n), "+v"(ln));
+        glcm_features_16<true>(own + (big ? (uint32_t)wave * NN : 0u), n, big ? 1 : K, big, fdst + (big ? 5 * wave : 0), ln);
+      }
     }
     // thread 0's number, to all
     __syncthreads();
