@@ -84,10 +84,17 @@ __host__ __device__ inline LevelChunk level_chunk(const LevelRect& r, int c) {
 // banks that move with a as well as with b.
 constexpr uint32_t level_pitch(uint32_t N) { return ((N + 1u) / 2u) | 1u; }
 
+// Most bands worth their sums: two steps of pairs each, or the one step of small
+// images (up to 8 bands).  Measured on MI355X, us a call, two steps; one: 300^2 N =
+// 200, two offsets 22.2; 18.3, N = 256, four 17.6; 16.0; 1024^2 N = 256, four 24.5;
+// 31.1.
+inline uint64_t level_most_bands(uint64_t chunks) {
+  return std::max<uint64_t>({1, chunks / (2 * kLevelThreads), std::min<uint64_t>(8, chunks / kLevelThreads)});
+}
+
 // Layout for `rows` first-pixel rows of width W of an image of `levels` levels
 // and K offsets: slices of whole rows of a GLCM that fit the LDS (lds_words), and
-// bands so that the workgroups fill the CUs once, each with at least two steps
-// of pairs.
+// bands so that the workgroups fill the CUs once.
 struct LevelLayout {
   int slices = 1, bands = 1;
   uint32_t slice_rows = 0, slice_dwords = 0, spill_cap = 0;
@@ -127,7 +134,7 @@ inline LevelLayout level_layout(int levels, int K, int W, int rows, int lds_word
   L.units = (uint64_t)K * (uint64_t)L.slices;
   L.chunks = (((uint64_t)W + 15) / 16) * (uint64_t)rows;
   const uint64_t fill = std::max<uint64_t>(1, (uint64_t)std::max(1, cus) * L.per_cu((uint64_t)lds_words) / L.units);
-  L.set_bands((int)std::min(fill, std::max<uint64_t>(1, L.chunks / (2 * kLevelThreads))));
+  L.set_bands((int)std::min(fill, level_most_bands(L.chunks)));
   return L;
 }
 
@@ -143,7 +150,7 @@ inline uint64_t level_reserve(int N, int K, int W, int H, int lds_words, int cus
     if (levels < N && L.slices != 1) continue;
     // workgroups and entries of their spill lists, whatever the offsets and rows of a call
     const uint64_t groups = std::min(std::max(L.units, (uint64_t)std::max(1, cus) * L.per_cu((uint64_t)lds_words)),
-                                     L.units * std::max<uint64_t>(1, L.chunks / (2 * kLevelThreads)));
+                                     L.units * level_most_bands(L.chunks));
     const uint64_t spills = L.units * (L.chunks / 2048 + 1) + 2 * groups;
     most = std::max(most, (groups * ((uint64_t)L.slice_dwords + 1) + spills) * 4u);
   }

@@ -93,9 +93,13 @@ __device__ __forceinline__ uint32_t varies(const uint32_t (&w)[D]) {
 // pair.
 //
 // A lane whose 16 first pixels have one level, and its 16 second pixels too,
-// adds 16 at once; when that holds for every lane of the wavefront (flat
+// adds its pairs at once; when that holds for every lane of the wavefront (flat
 // regions, where all lanes vote one bin and each atomic takes 128 cycles), a
-// step is one atomic instead of 16.
+// step is one atomic instead of 16, also where a row ends in the wavefront (a
+// lane then has fewer than 16 pairs): that is every step of rows up to 1024
+// pixels.  Constant images, us a call, without and with the shortcut at row ends:
+// 300^2 N = 256, one offset 49; 16, 1024^2 42; 17, 4096^2 with 12 offsets 310; 150
+// (other images 114; 118).
 //
 // A 16-bit bin must stay below 2^16: with every bin below m, m + 2^14 s bounds
 // it after s steps.  Every two steps (three while no bin has reached 2^14) the
@@ -106,8 +110,8 @@ __device__ __forceinline__ uint32_t varies(const uint32_t (&w)[D]) {
 // Bound: LDS atomics on random banks (one copy of the bins: the fullest of 32
 // banks serves three or four of 32 lanes, about 16 cycles per wavefront
 // instruction).  Measured on MI355X, 4096^2 u8 smooth, N = 256, 12 offsets (2.0e8
-// pairs): 107 us, 20 cycles a wavefront instruction with the looks at the bins
-// and the ends; 111 us with an even row pitch.  The kernel before it, ten
+// pairs): 112 us, 21 cycles a wavefront instruction with the looks at the bins
+// and the ends; 4 us more with an even row pitch.  The kernel before it, ten
 // ranges of the 12 GLCMs' bins over the whole image each, took 449 us.
 template <typename Pix, bool BYTE, bool SLICED>
 __global__ __launch_bounds__(kLevelThreads) void k_vote_levels(LevelArgs a) {
@@ -181,6 +185,13 @@ __global__ __launch_bounds__(kLevelThreads) void k_vote_levels(LevelArgs a) {
         mixed = varies<(int)sizeof(Pix)>(p1.w) | varies<(int)sizeof(Pix)>(p2.w);
       fetch();
       if (__any(me.skip != 0 || me.n != kLevelChunk)) {
+        if (__builtin_expect(__builtin_amdgcn_readfirstlane((int)mixed) == 0 && !__any(mixed != 0u && me.n != 0), 0)) {
+          const uint32_t av = f.get(0) - a0, w2 = base + av * pitch + 2u * g.get(0);
+          if (me.n > me.skip && (!SLICED || av < rows))
+            __hip_atomic_fetch_add((lds_word_t*)(size_t)(w2 & ~3u), (uint32_t)(me.n - me.skip) << ((w2 << 3) & 31u),
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          continue;
+        }
 #pragma unroll
         for (int t = 0; t < kLevelChunk; ++t) {
           const uint32_t av = f.get(t) - a0, w2 = base + av * pitch + 2u * g.get(t);
