@@ -207,6 +207,7 @@ struct glcm_plan_s {
   uint32_t* xbuf = nullptr;  // [kXcdSlots][K*N*N] accumulation slices, kept zero between calls
   uint32_t xslots = glcm::kXcdSlots;  // slices the device's XCC_IDs reach (the rest stay zero)
   bool no_alloc = false;  // a transient plan of compute_in_workspace: never allocate (no staging copy)
+  uint64_t scratch_bytes = 0;  // its caller's memory, the slices first
   glcm::LevelStore levels;         // the level-slice kernel's partials
   size_t levels_most = SIZE_MAX;   // most bytes the plan may take for them (glcm::limit_levels)
 
@@ -758,9 +759,9 @@ int count_levels(glcm_plan_t p, const VoteArgs& v, int b, uint32_t* out, bool ac
   }
   uint32_t* mem = nullptr;
   if (p->no_alloc) {
-    // the caller's accumulation slices serve as partials (no other kernel of
-    // this call uses them)
-    if (!L.fit((uint64_t)glcm::kXcdSlots * v.words_total * 4u)) return GLCM_OK;
+    // the caller's memory serves as partials (no other kernel of this call uses
+    // the slices)
+    if (!L.fit(p->scratch_bytes)) return GLCM_OK;
     mem = p->xbuf;
   } else {
     if (!hold_levels(p, &stream) || !L.fit(p->levels.bytes)) return GLCM_OK;
@@ -1790,6 +1791,7 @@ int compute_in_workspace(uint32_t* slices, size_t slice_words, const void* img, 
   p.xbuf = slices;
   p.xslots = kXcdSlots;
   p.no_alloc = true;
+  p.scratch_bytes = (uint64_t)slice_words * 4u;
   // the slices start at zero whatever an earlier call left (a fill kernel:
   // the call stays capturable in a graph)
   GLCM_TRY(launch_zero(slices, (uint64_t)kXcdSlots * words, stream));
