@@ -327,8 +327,8 @@ __device__ __forceinline__ double neg_plogp(double p, const LogPoint* t) { retur
 //     HXY1 = -sum p ln(px py) = HX + HY,  HXY2 = -sum px py ln(px py) = HX + HY.
 // With a marginal on a single level p = px py, so f12 and f13 are 0 (and f3 is
 // 1 by definition).
-// The covariance is never taken as a difference of second moments in floating
-// point: where the two marginals lie apart those are near N^2 and cancel (4e9
+// The covariance is a difference of whole numbers below 2^53, or summed about the
+// means, never a difference of rounded second moments: where the two marginals lie apart those are near N^2 and cancel (4e9
 // counts in a corner left f3 at 0.20 instead of 0.289).
 // ---------------------------------------------------------------------------
 struct Moments {
@@ -544,15 +544,11 @@ __global__ __launch_bounds__(kStatsThreads, L == 16 ? 4 : 3) void k_haralick_wav
 // Bound: VALU issue and the LDS of the one CU that holds the matrix.
 // Measured on MI355X, 12 matrices of N = 256: 51 us (282 us with 256 threads,
 // a thread per diagonal and three logarithm terms a bin).
-template <int W, typename C>
-__device__ __forceinline__ void haralick_bins(const uint32_t* P, int N, double T, double inv, C* ps, C* pd,
-                                              const LogPoint* table, double mux, double muy, double& sq, double& ent,
-                                              double& cov) {
+template <int W>
+__device__ __forceinline__ void haralick_bins(const uint32_t* P, int N, double T, double inv, uint32_t* ps, uint32_t* pd,
+                                              const LogPoint* table, double& sq, double& ent) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (int j0 = 0; j0 < N; j0 += 256) {
-    double dj[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) dj[e] = (double)(j0 + 64 * e + lane) - muy;
     uint32_t next[4];
     auto load = [&](int i) {
 #pragma unroll
@@ -568,22 +564,45 @@ __device__ __forceinline__ void haralick_bins(const uint32_t* P, int N, double T
 #pragma unroll
       for (int e = 0; e < 4; ++e) c[e] = next[e];
       load(i + W);
-      double along = 0.0;  // sum of (j - muy) p along the row
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int j = j0 + 64 * e + lane;
         if (c[e] != 0u) {
-          __hip_atomic_fetch_add(&ps[i + j], (C)c[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-          __hip_atomic_fetch_add(&pd[i > j ? i - j : j - i], (C)c[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          __hip_atomic_fetch_add(&ps[i + j], c[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          __hip_atomic_fetch_add(&pd[i > j ? i - j : j - i], c[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
           double p = (double)c[e] * inv;
           p = fma(fma(-p, T, (double)c[e]), inv, p);
           sq += p * p;
           ent -= p * log_tab(p, table);
-          along = fma(p, dj[e], along);
         }
       }
-      cov = fma((double)i - mux, along, cov);
     }
+  }
+}
+
+// The same for 2^32 counts and more, where sum i j c is no longer a whole number
+// below 2^53: the covariance is summed about the means.  (Rare, so a bin at a time
+// with few registers.)
+template <int W>
+__device__ __forceinline__ void haralick_bins_wide(const uint32_t* P, int N, double T, double inv, unsigned long long* ps,
+                                                   unsigned long long* pd, const LogPoint* table, double mux, double muy,
+                                                   double& sq, double& ent, double& cov) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll 1
+  for (int i = wave; i < N; i += W) {
+    double along = 0.0;
+#pragma unroll 1
+    for (int j = lane; j < N; j += 64) {
+      const uint32_t c = P[(size_t)i * N + j];
+      if (c == 0u) continue;
+      __hip_atomic_fetch_add(&ps[i + j], (unsigned long long)c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      __hip_atomic_fetch_add(&pd[i > j ? i - j : j - i], (unsigned long long)c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      const double p = quotient((double)c, T, inv);
+      sq += p * p;
+      ent -= p * log_tab(p, table);
+      along = fma(p, (double)j - muy, along);
+    }
+    cov = fma((double)i - mux, along, cov);
   }
 }
 
@@ -609,9 +628,9 @@ __global__ __launch_bounds__(64 * W) void k_haralick(StatsArgs a) {
     for (int t = threadIdx.x; t < N; t += 64 * W) row[t] = col[t] = 0.0;
     for (int t = threadIdx.x; t < 3 * N - 1; t += 64 * W) ps[t] = 0;
     __syncthreads();
-    double T = 0.0;
+    double T = 0.0, cov = 0.0;  // cov: sum i j c (whole numbers below 2^53 for fewer than 2^32 counts)
     for (int j0 = 0; j0 < N; j0 += 256) {
-      double cs[4] = {0.0, 0.0, 0.0, 0.0};
+      double cs[4] = {0.0, 0.0, 0.0, 0.0}, is[4] = {0.0, 0.0, 0.0, 0.0};
       for (int i = wave; i < N; i += W) {
         double s = 0.0;
 #pragma unroll
@@ -619,6 +638,7 @@ __global__ __launch_bounds__(64 * W) void k_haralick(StatsArgs a) {
           const int j = j0 + 64 * e + lane;
           const double c = j < N ? (double)P[(size_t)i * N + j] : 0.0;
           cs[e] += c;
+          is[e] = fma((double)i, c, is[e]);
           s += c;
         }
         s = wave_sum(s);
@@ -628,6 +648,7 @@ __global__ __launch_bounds__(64 * W) void k_haralick(StatsArgs a) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int j = j0 + 64 * e + lane;
+        cov = fma((double)j, is[e], cov);
         if (j < N && cs[e] != 0.0) __hip_atomic_fetch_add(&col[j], cs[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       }
     }
@@ -642,19 +663,18 @@ __global__ __launch_bounds__(64 * W) void k_haralick(StatsArgs a) {
     }
     const double inv = 1.0 / T;
     const bool narrow = T <= 4294967295.0;
-    // the marginals' means, by every wavefront (the covariance is summed about them)
-    double mux = 0.0, muy = 0.0;
-    for (int t = lane; t < N; t += 64) {
-      mux = fma((double)t, row[t], mux);
-      muy = fma((double)t, col[t], muy);
+    double sq = 0.0, ent = 0.0;
+    if (narrow) {
+      haralick_bins<W>(P, N, T, inv, ps32, pd32, table, sq, ent);
+    } else {
+      double mux = 0.0, muy = 0.0;  // by every wavefront
+      for (int t = lane; t < N; t += 64) {
+        mux = fma((double)t, row[t], mux);
+        muy = fma((double)t, col[t], muy);
+      }
+      cov = 0.0;
+      haralick_bins_wide<W>(P, N, T, inv, ps, pd, table, wave_sum(mux) * inv, wave_sum(muy) * inv, sq, ent, cov);
     }
-    mux = wave_sum(mux) * inv;
-    muy = wave_sum(muy) * inv;
-    double sq = 0.0, ent = 0.0, cov = 0.0;
-    if (narrow)
-      haralick_bins<W, uint32_t>(P, N, T, inv, ps32, pd32, table, mux, muy, sq, ent, cov);
-    else
-      haralick_bins<W, unsigned long long>(P, N, T, inv, ps, pd, table, mux, muy, sq, ent, cov);
     sq = wave_sum(sq);
     ent = wave_sum(ent);
     cov = wave_sum(cov);
@@ -667,16 +687,15 @@ __global__ __launch_bounds__(64 * W) void k_haralick(StatsArgs a) {
     // distribution `task` (0 rows, 1 columns, 2 |i - j|, 3 i + j) by W / 4 wavefronts
     constexpr int G = W / 4;
     const int task = wave / G, first = (wave % G) * 64 + lane, n = task == 3 ? 2 * N - 1 : N;
-    auto entry = [&](int t) {
-      const double c = task == 0 ? row[t] : (task == 1 ? col[t]
+    auto count = [&](int t) {
+      return task == 0 ? row[t] : (task == 1 ? col[t]
                        : (task == 2 ? (narrow ? (double)pd32[t] : (double)pd[t]) : (narrow ? (double)ps32[t] : (double)ps[t])));
-      return quotient(c, T, inv);
     };
     double mean = 0.0, h = 0.0, con = 0.0, idm = 0.0;
     int occ = 0;
     for (int t = first; t < n; t += 64 * G) {
-      const double x = entry(t), d = (double)t;
-      mean += d * x;
+      const double c = count(t), x = quotient(c, T, inv), d = (double)t;
+      mean = fma(d, narrow ? c : x, mean);
       con += d * d * x;
       idm += x / (1.0 + d * d);
       h += neg_plogp(x, table);
@@ -695,10 +714,11 @@ __global__ __launch_bounds__(64 * W) void k_haralick(StatsArgs a) {
     mean = 0.0;
 #pragma unroll
     for (int w = 0; w < G; ++w) mean += sums[task * G + w][0];
+    if (narrow) mean = quotient(mean, T, inv);  // (of whole numbers: exact for a single level)
     double var = 0.0;
     for (int t = first; t < n; t += 64 * G) {
       const double d = (double)t - mean;
-      var += d * d * entry(t);
+      var += d * d * quotient(count(t), T, inv);
     }
     var = wave_sum(var);
     if (lane == 0) sums[wave][4] = var;
@@ -725,7 +745,8 @@ __global__ __launch_bounds__(64 * W) void k_haralick(StatsArgs a) {
       s.hy = over(1, 1); s.vy = over(1, 4);
       s.hd = over(2, 1); s.vd = over(2, 4);
       s.contrast = over(2, 2); s.idm = over(2, 3);
-      s.sa = over(3, 0); s.hs = over(3, 1); s.vs = over(3, 4);
+      if (narrow) s.cov = difference_of_products(T, s.cov, over(0, 0), over(1, 0)) * inv * inv;
+      s.sa = narrow ? over(3, 0) / T : over(3, 0); s.hs = over(3, 1); s.vs = over(3, 4);
       s.one = ox == 1 || oy == 1;
       haralick_store(s, s.vx, f);
     }
