@@ -50,6 +50,12 @@ __device__ __forceinline__ uint32_t word_of(int lane, int v) {
   return VEC ? 4u * (uint32_t)lane + 256u * (uint32_t)(v >> 2) + (uint32_t)(v & 3) : (uint32_t)lane + 64u * (uint32_t)v;
 }
 
+// Whether any lane has a word v (the same on every lane: N = 17 needs 5 of 16).
+template <bool VEC>
+__device__ __forceinline__ bool has_word(uint32_t NN, int v) {
+  return (VEC ? 256u * (uint32_t)(v >> 2) : 64u * (uint32_t)v) < NN;
+}
+
 template <int L, bool VEC>
 __device__ __forceinline__ void load_matrix(uint32_t (&c)[kWords<L>], const uint32_t* P, uint32_t NN, int lane) {
   if constexpr (VEC) {
@@ -64,7 +70,8 @@ __device__ __forceinline__ void load_matrix(uint32_t (&c)[kWords<L>], const uint
 #pragma unroll
     for (int v = 0; v < kWords<L>; ++v) {
       const uint32_t r = word_of<false>(lane, v);
-      c[v] = r < NN ? P[r] : 0u;
+      c[v] = 0u;
+      if (has_word<false>(NN, v) && r < NN) c[v] = P[r];
     }
   }
 }
@@ -82,7 +89,7 @@ __device__ __forceinline__ void store_matrix(T* out, const T (&s)[kWords<L>], ui
 #pragma unroll
     for (int v = 0; v < kWords<L>; ++v) {
       const uint32_t r = word_of<false>(lane, v);
-      if (r < NN) out[r] = s[v];
+      if (has_word<false>(NN, v) && r < NN) out[r] = s[v];
     }
   }
 }
@@ -109,12 +116,14 @@ __global__ __launch_bounds__(kStatsThreads) void k_symmetrize_wave(StatsArgs a) 
     wave_sync_lds();  // the previous matrix's reads of M are done
 #pragma unroll
     for (int v = 0; v < kWords<L>; ++v) {
+      if (!has_word<VEC>(NN, v)) break;
       const uint32_t r = word_of<VEC>(lane, v), i = divide(r, a.nmagic, a.nshift);
       if (r < NN) M[i * p + (r - i * N)] = c[v];
     }
     wave_sync_lds();
 #pragma unroll
     for (int v = 0; v < kWords<L>; ++v) {
+      if (!has_word<VEC>(NN, v)) break;
       const uint32_t r = word_of<VEC>(lane, v), i = divide(r, a.nmagic, a.nshift);
       if (r < NN) c[v] += M[(r - i * N) * p + i];
     }
@@ -122,7 +131,40 @@ __global__ __launch_bounds__(kStatsThreads) void k_symmetrize_wave(StatsArgs a) 
   }
 }
 
-// N > 32: one workgroup per pair of 32 x 32 tiles (I, J), I <= J, of a matrix.
+// 32 < N <= 48: a workgroup per matrix, staged whole (an odd pitch, so the
+// transposed reads spread over the banks); in == out is safe.  By tiles N = 33
+// wastes most of two of its three pairs: 4096 matrices 14.0 us, staged 11.7, N = 48
+// 17.4 and 14.7; 16384 of N = 33 42.8 and 24.7.
+constexpr int kStagedMaxN = 48;
+__global__ __launch_bounds__(kStatsThreads) void k_symmetrize_staged(StatsArgs a) {
+  __shared__ uint32_t M[kStagedMaxN * (kStagedMaxN + 1)];
+  const uint32_t N = (uint32_t)a.N, NN = N * N, p = lds_pitch(N);
+  constexpr int kMost = (kStagedMaxN * kStagedMaxN + kStatsThreads - 1) / kStatsThreads;
+  for (int k = blockIdx.x; k < a.K; k += gridDim.x) {
+    const uint32_t* P = a.in + (size_t)k * NN;
+    uint32_t* S = a.out_u + (size_t)k * NN;
+    uint32_t c[kMost];
+#pragma unroll
+    for (int v = 0; v < kMost; ++v) {
+      const uint32_t r = threadIdx.x + (uint32_t)(v * kStatsThreads);
+      c[v] = r < NN ? P[r] : 0u;
+    }
+    __syncthreads();  // the previous matrix's reads are done
+#pragma unroll
+    for (int v = 0; v < kMost; ++v) {
+      const uint32_t r = threadIdx.x + (uint32_t)(v * kStatsThreads), i = divide(r, a.nmagic, a.nshift);
+      if (r < NN) M[i * p + (r - i * N)] = c[v];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int v = 0; v < kMost; ++v) {
+      const uint32_t r = threadIdx.x + (uint32_t)(v * kStatsThreads), i = divide(r, a.nmagic, a.nshift);
+      if (r < NN) S[r] = c[v] + M[(r - i * N) * p + i];
+    }
+  }
+}
+
+// N > 48: one workgroup per pair of 32 x 32 tiles (I, J), I <= J, of a matrix.
 // Both tiles are read before either is written, and no other workgroup
 // touches them, so in == out is safe.  12 matrices of N = 256 on MI355X: 4.4
 // us (63 us with one workgroup a matrix).
@@ -209,15 +251,16 @@ __global__ __launch_bounds__(kStatsThreads) void k_probability_wave(StatsArgs a)
 // thread (integers below 2^53: exact in any order).
 template <int W>
 __device__ __forceinline__ double total_wg(const uint32_t* P, uint32_t n, bool vec, double* part) {
+  constexpr int kUnroll = W == 4 ? 4 : 8;
   double t = 0.0;
   if (vec) {
-#pragma unroll 8
+#pragma unroll kUnroll
     for (uint32_t r = 4u * threadIdx.x; r < n; r += 4u * 64u * W) {
       const uint4 v = *(const uint4*)(P + r);
       t += ((double)v.x + (double)v.y) + ((double)v.z + (double)v.w);
     }
   } else {
-#pragma unroll 8
+#pragma unroll kUnroll
     for (uint32_t r = threadIdx.x; r < n; r += 64u * W) t += (double)P[r];
   }
   t = wave_sum(t);
@@ -237,9 +280,9 @@ __device__ __forceinline__ double total_wg(const uint32_t* P, uint32_t n, bool v
 // four in 15.5 us (82 and 326 us with one workgroup of 256 threads each).
 constexpr int kWideWaves = 16;
 
-template <bool AVG>
-__global__ __launch_bounds__(64 * kWideWaves) void k_probability_wg(StatsArgs a) {
-  __shared__ double part[kWideWaves];
+template <bool AVG, int W>
+__global__ __launch_bounds__(64 * W) void k_probability_wg(StatsArgs a) {
+  __shared__ double part[W];
   __shared__ double totals[AVG ? kAverageMaxGroup : 1][2];
   const uint32_t NN = (uint32_t)a.N * (uint32_t)a.N;
   const uint64_t units = (uint64_t)(a.K / a.m) * a.parts;
@@ -252,7 +295,7 @@ __global__ __launch_bounds__(64 * kWideWaves) void k_probability_wg(StatsArgs a)
     if (AVG) {
       __syncthreads();  // the previous unit's readers are done with totals
       for (int q = 0; q < a.m; ++q) {
-        const double t = total_wg<kWideWaves>(P + (size_t)q * NN, NN, a.vec != 0, part);
+        const double t = total_wg<W>(P + (size_t)q * NN, NN, a.vec != 0, part);
         if (threadIdx.x == 0) {
           totals[q][0] = t == 0.0 ? 1.0 : t;
           totals[q][1] = t == 0.0 ? 1.0 : 1.0 / t;
@@ -265,7 +308,7 @@ __global__ __launch_bounds__(64 * kWideWaves) void k_probability_wg(StatsArgs a)
         o[w] = (float)(acc / (double)a.m);
       }
     } else {
-      double t = total_wg<kWideWaves>(P, NN, a.vec != 0, part);
+      double t = total_wg<W>(P, NN, a.vec != 0, part);
       if (t == 0.0) t = 1.0;
       const double r = 1.0 / t;
 #pragma unroll 4
@@ -783,11 +826,28 @@ void split(StatsArgs* a, uint64_t groups) {
   a->parts = (uint32_t)((NN + a->share - 1) / a->share);
 }
 
+// Small matrices leave four wavefronts enough to do, and more workgroups fit.
+// Measured on MI355X, us a call, sixteen; four wavefronts: 4096 matrices normalised
+// N = 33 23.8; 13.0, N = 64 33.3; 29.8, 4096 averaged by four N = 33 15.4; 12.8, N = 44
+// 17.0; 18.1 (16384: 59.6; 55.0), N = 48 18.2; 20.9; few matrices the same.
+template <bool AVG>
+void launch_probability(const StatsArgs& a, uint64_t groups, hipStream_t stream) {
+  const dim3 grid(grid_for(groups * a.parts, 8192));
+  if (a.N <= (AVG ? 44 : 64))
+    hipLaunchKernelGGL((k_probability_wg<AVG, 4>), grid, dim3(256), 0, stream, a);
+  else
+    hipLaunchKernelGGL((k_probability_wg<AVG, kWideWaves>), grid, dim3(64 * kWideWaves), 0, stream, a);
+}
+
 }  // namespace
 
 hipError_t launch_symmetrize(const StatsArgs& a, hipStream_t stream) {
   if (a.N <= kWaveMaxN) {
     GLCM_WAVE_LAUNCH(k_symmetrize_wave, a.K, a.out_u, );
+    return hipGetLastError();
+  }
+  if (a.N <= kStagedMaxN) {
+    hipLaunchKernelGGL(k_symmetrize_staged, dim3(grid_for((uint64_t)a.K, 8192)), dim3(kStatsThreads), 0, stream, a);
     return hipGetLastError();
   }
   const uint64_t nt = ((uint64_t)a.N + kTile - 1) / kTile, pairs = nt * (nt + 1) / 2, units = pairs * (uint64_t)a.K;
@@ -805,8 +865,7 @@ hipError_t launch_normalize(const StatsArgs& a0, hipStream_t stream) {
   }
   a.vec = vec_ok(a, a.in) ? 1 : 0;
   split(&a, (uint64_t)a.K);
-  hipLaunchKernelGGL(k_probability_wg<false>, dim3(grid_for((uint64_t)a.K * a.parts, 8192)), dim3(64 * kWideWaves), 0,
-                     stream, a);
+  launch_probability<false>(a, (uint64_t)a.K, stream);
   return hipGetLastError();
 }
 
@@ -819,8 +878,7 @@ hipError_t launch_average(const StatsArgs& a0, hipStream_t stream) {
   a.vec = vec_ok(a, a.in) ? 1 : 0;
   const uint64_t groups = (uint64_t)(a.K / a.m);
   split(&a, groups);
-  hipLaunchKernelGGL(k_probability_wg<true>, dim3(grid_for(groups * a.parts, 8192)), dim3(64 * kWideWaves), 0, stream,
-                     a);
+  launch_probability<true>(a, groups, stream);
   return hipGetLastError();
 }
 
