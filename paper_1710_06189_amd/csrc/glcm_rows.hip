@@ -237,9 +237,15 @@ __global__ __launch_bounds__(rows_max_threads(sizeof(Pix), MAXDY, UNAL)) void k_
   const int y0 = a.y_begin + region * a.region_rows;
   const int y1 = min(a.y_end, y0 + a.region_rows);
   const int spans = (a.W + 1023) >> 10, rows_here = y1 - y0;
-  // runs of a span: as many as there are wavefronts for it, of whole rows
+  // runs of a span: as many as there are wavefronts for it, of whole rows (with
+  // three spans for sixteen wavefronts one is left over).  With three GLCMs or
+  // fewer a run is not shorter than the MAXDY rows below it, which it reads and
+  // quantizes too: its votes take no longer than that.  Measured on MI355X, us a
+  // call, any length; MAXDY rows at least: N = 100, twelve offsets (three a
+  // partition) 1000^2 46.8; 43.7; but N = 32, twelve (six) 300^2 19.3; 21.3, N = 64
+  // 1000^2 33.5; 37.2.
   const int per_span = max(1, nwaves / spans);
-  const int run_rows = max(1, (rows_here + per_span - 1) / per_span);
+  const int run_rows = max(kp1 - kp0 <= 3 ? MAXDY : 1, (rows_here + per_span - 1) / per_span);
   const int runs = (rows_here + run_rows - 1) / run_rows;  // (none where rows_here <= 0)
   constexpr int NROWS = RPW + MAXDY;
 
