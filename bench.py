@@ -50,7 +50,7 @@ METRIC = "Gpairs/s & % HBM roofline (bit-exact); batched vs per-image; p50/p99 l
 HBM_PEAK_GBS = 8000.0
 # sources of the vote kernel (the dominant kernel the traffic record describes)
 VOTE_SOURCES = [os.path.join(ROOT, "paper_1710_06189_amd", "csrc", f)
-                for f in ("glcm_vote.hip", "glcm_device.h", "glcm_internal.h")]
+                for f in ("glcm_vote.hip", "glcm_merge.h", "glcm_device.h", "glcm_internal.h")]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "vote_strips_4096x4096_u8_smooth_traffic.json")
 # the same for the block-code kernel (the autotuner's pick on smooth images)
 BLOCK_SOURCES = [os.path.join(ROOT, "paper_1710_06189_amd", "csrc", f)
@@ -62,7 +62,7 @@ HIST_SOURCES = [os.path.join(ROOT, "paper_1710_06189_amd", "csrc", f)
 HIST_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "histogram_4096x4096_u8_smooth_traffic.json")
 # VALU instruction count of the Haralick kernel (an fp64 ALU-bound kernel)
 STATS_SOURCES = [os.path.join(ROOT, "paper_1710_06189_amd", "csrc", f)
-                 for f in ("glcm_stats.hip", "glcm_device.h", "glcm_stats.h", "glcm_internal.h")]
+                 for f in ("glcm_stats.hip", "glcm_wave.h", "glcm_device.h", "glcm_stats.h", "glcm_internal.h")]
 HARALICK_VALU_FILE = os.path.join(ROOT, "profiles", "haralick_16384x16x16_glcm_like_valu.json")
 # VALU issue peak: 256 CUs x 2.4 GHz x one wave64 instruction per CU-cycle
 # (four SIMDs, each finishing a 64-lane instruction every 4 cycles on 16 lanes)

@@ -107,7 +107,7 @@ typedef struct glcm_tuning {
     int wg_size;        /* threads per workgroup: 256, 512 or 1024 (the strip kernel runs
                            at most 512 on uint16 images with offsets reaching 2 pixels and
                            on any image with offsets reaching 3 or 4) */
-    int rows_per_wave;  /* slab kernel: first-pixel rows per wavefront slab (4); 0 elsewhere */
+    int rows_per_wave;  /* slab kernel: 4 (or 0, the same), a fixed value; 0 elsewhere */
     int tile_rows;      /* host-image upload tile height (rows) */
     int counter_bits;   /* LDS counters: 16 or 32; 0 keeps the current value.  Slab kernel:
                            two copies per dword; strip kernel: two GLCMs per dword (dwords
@@ -302,10 +302,10 @@ GLCM_API int glcm_compute(glcm_plan_t plan, const void *img, int W, int H, int64
  * entropy (natural log), homogeneity (inverse difference moment,
  * 1/(1+(i-j)^2)), correlation.  p = P/T with T = sum of P[k].  T = 0 gives
  * five zeros; a row or column marginal with a single occupied level gives
- * correlation 1.  Energy, entropy and homogeneity are fp32 terms summed in
- * fp64; the contrast and the correlation come from exact integer moments (the contrast
- * as one fp64 quotient, the correlation's variances and covariance combined
- * in fp64).
+ * correlation 1.  The contrast, the energy and the correlation come from exact
+ * sums of the counts (one fp64 quotient; the correlation's variances and
+ * covariance combined in fp64), entropy and homogeneity from fp32 logarithms and
+ * quotients of the exact counts, summed in fp64 and divided by T once.
  *
  *   glcm     device memory, K*N*N uint32 (the layout glcm_compute writes).
  *   out      device memory, K*5 float, overwritten.
@@ -503,7 +503,8 @@ GLCM_API int glcm_batch_tuning(glcm_plan_t plan, glcm_batch_tuning_t *tuning, in
  * (glcm_batch_compute, glcm_batch_prepare).  tiles, T, lo, hi as for
  * glcm_batch_compute; repeats 1 .. 1000.  Allocates its own outputs and stream
  * and synchronises before returning.  *chosen (may be NULL) receives the
- * layout kept.  Errors as for glcm_batch_compute; on a HIP failure the plan
+ * layout kept as glcm_batch_tuning reads it (for the default the LDS layout that
+ * would run without the matrix cores; 0, 0, 0 asks another plan for the default).  Errors as for glcm_batch_compute; on a HIP failure the plan
  * keeps its previous layout.
  */
 GLCM_API int glcm_batch_autotune(glcm_plan_t plan, const glcm_tile_t *tiles, int T, uint32_t lo, uint32_t hi,

@@ -475,11 +475,13 @@ int onehot_segment_rows(int windows, int rows, bool last, int reach, int64_t wav
   }
 }
 
-// Image passes of the partitioned kernel worth one GLCM's pairs added into
-// the per-XCD L2 slices: measured on MI355X, 4096^2 u8 images, a pass costs
-// 0.04-0.05 ms and a GLCM in the slices 0.63 ms on noise (more on smooth
-// images, where the slice atomics collide: 0.5-1.5 ms).  The slices take
-// over beyond this many passes per GLCM.
+// Ranges of 16-bit bins (an LDS full of them) per GLCM up to which the
+// partitioned path counts, above which pairs are added into the per-XCD L2 slices:
+// N up to 1020 or so.  The number is of a kernel that walked the image once per
+// range and is kept as the plans' rule.  For the level slices that count there now
+// it lies too low: measured on MI355X, 4096^2, one offset, us a call, level slices at
+// N = 1024; L2 slices at N = 1040 (u8 noise, smooth, constant) 80, 79, 170; 665, 1086,
+// 23792, u16 182, 182, 390; 644, 788, 23815.
 constexpr int kPassesPerSliceGlcm = 13;
 
 // Shortest run of rows a wavefront segment of the batch kernel walks, unless
@@ -598,12 +600,13 @@ int choose_tuning(glcm_plan_t p, glcm_tuning_t* t) {
     } else {
       uint64_t P1 = (words + budget - 1) / budget;
       if (p->flags & GLCM_FLAG_FORCE_PARTITIONED) P1 = std::max<uint64_t>(P1, std::min<uint64_t>(words, 3));
-      // the passes the partitioned kernel runs: half as many with 16-bit
-      // counters, which need the XCD slices and rows below 2^16 pixels
+      // the ranges of bins the LDS holds: half as many with 16-bit bins (level
+      // slices), which need the XCD slices' plans; rows of 2^16 pixels and more
+      // keep the rule of 32-bit bins, though the level slices take any width
       const bool c16 = P1 > 1 && l2_slices_fit(p) && p->max_W <= 65535;
       const uint64_t passes = c16 ? (words + 2 * budget - 1) / (2 * budget) : P1;
       if (passes > (uint64_t)kPassesPerSliceGlcm * (uint64_t)p->K) {
-        // more LDS passes than pay off: pairs straight into the per-XCD
+        // (kPassesPerSliceGlcm) pairs straight into the per-XCD
         // slices when they fit (never slower than device-wide atomics on
         // MI355X, faster on smooth images), else device-wide atomics
         d.path = l2_slices_fit(p) ? kPathL2 : kPathGlobal;
@@ -615,9 +618,7 @@ int choose_tuning(glcm_plan_t p, glcm_tuning_t* t) {
         d.path = P1 > 1 ? kPathPartitioned : kPathGeneric;
         d.replicas = R;
         d.partitions = (int)P1;
-        // several bin partitions with one copy: 16-bit counters, two bins per
-        // dword, half the passes (faster on smooth images; on noise the
-        // shorter bands' merge can cost more, which the autotuner weighs)
+        // several bin partitions with one copy: level slices of 16-bit bins
         if (P1 > 1 && R == 1) d.counter_bits = 16;
       }
     }
@@ -858,7 +859,6 @@ int count_onehot(glcm_plan_t p, const VoteArgs& v, int b, uint32_t* out, bool ac
   a.words_total = v.words_total;
   a.xbuf = single ? nullptr : p->xbuf;
   a.out = out;
-  a.accumulate = 0;
   glcm::LaunchTiming tm;
   if (p->flags & GLCM_FLAG_TIMING) {
     GLCM_TRY(hipEventCreate(&tm.start));
@@ -898,9 +898,6 @@ int count_device(glcm_plan_t p, const void* img, int W, int H, int64_t stride, i
   a.y_begin = y_begin;
   a.y_end = y_end;
   a.q = make_quant(p->N, lo, hi);
-  // x / N and x / N^2 as multiply-high + shift: make_quant(1, 0, d - 1) has
-  // D = d and the same division constants
-  a.div_n = make_quant(1, 0, (uint32_t)p->N - 1);
   fast_quant(b, p->N, lo, hi, &a.qfast, &a.qfast_shift, &a.qfast_mask);
   a.K = p->K;
   a.words_total = words;
@@ -996,7 +993,9 @@ int count_device(glcm_plan_t p, const void* img, int W, int H, int64_t stride, i
     ba.tmask = c.tmask;
     ba.nbins = 16u * (uint32_t)p->N + 6u;
     ba.fb_copies = block_fb_copies(p);
-    ba.div_n = a.div_n;
+    // x / N as multiply-high + shift: make_quant(1, 0, N - 1) has D = N and the same
+    // division constants
+    ba.div_n = make_quant(1, 0, (uint32_t)p->N - 1);
     ba.words_total = words;
     ba.xbuf = p->xbuf;
     // bands: one workgroup of 16 wavefronts per band, as many bands as the
@@ -1053,7 +1052,6 @@ int count_device(glcm_plan_t p, const void* img, int W, int H, int64_t stride, i
   int log2R = 0;
   while ((1 << log2R) < R) ++log2R;
   a.log2R = log2R;
-  const int rpw = 4;
   // strip kernel: layout, template reach (1, 2 or 4) and workgroup size
   StripLayout sl;
   const int smd = strip_reach(c);
@@ -1117,7 +1115,6 @@ int count_device(glcm_plan_t p, const void* img, int W, int H, int64_t stride, i
   }
   a.nregions = nregions;
   a.region_rows = region_rows;
-  a.rows_per_wave = rpw;
 
   if (xcd) {
     a.xbuf = p->xbuf;
@@ -1130,11 +1127,11 @@ int count_device(glcm_plan_t p, const void* img, int W, int H, int64_t stride, i
   // LDS: the copies (at least one word per thread)
   size_t lds_bytes = ((size_t)a.part_words << log2R) * 4u;
   if (path == kPathRows) {
-    // 16-bit counters only when no count can reach 2^16: each slab gives a
-    // copy at most 64 lanes / R x 16 pixels x 4 rows votes into one bin.
+    // 16-bit counters only when no count can reach 2^16: a copy gets the votes of
+    // 64 / R lanes, 16 pixels each, of every span of every row (counted in fours)
     int bits = t.counter_bits == 16 && R >= 2 ? 16 : 32;
     const uint64_t chunks = ((uint64_t)W + 15) / 16, spans = (chunks + 63) / 64;
-    const uint64_t slabs = spans * (((uint64_t)a.region_rows + rpw - 1) / rpw);
+    const uint64_t slabs = spans * (((uint64_t)a.region_rows + 3) / 4);
     if (bits == 16 && slabs * 4096u / (uint64_t)R > 65535u) {
       bits = 32;  // same LDS footprint with half the copies
       R /= 2;
@@ -1159,7 +1156,7 @@ int count_device(glcm_plan_t p, const void* img, int W, int H, int64_t stride, i
   if (path == kPathStrips) {
     e = glcm::launch_vote_strips(a, b, smd, sl.D, wg, lds_bytes, stream, tm);
   } else if (path == kPathRows) {
-    e = glcm::launch_vote_rows(a, b, maxdy, rpw, wg, lds_bytes, stream, tm);
+    e = glcm::launch_vote_rows(a, b, maxdy, wg, lds_bytes, stream, tm);
   } else {
     e = glcm::launch_vote_generic(a, b, wg, lds_bytes, stream, tm);
   }

@@ -55,9 +55,7 @@ struct VoteArgs {
   int P;                      // bin partitions
   int nregions;               // row bands; workgroup g counts band g / P, partition g % P
   int region_rows;            // first-pixel rows per band
-  int rows_per_wave;          // row kernel: first-pixel rows per wavefront slab (4)
   uint32_t pitch;             // row kernel: LDS row pitch of a GLCM, >= N + 1 (row/column N: sentinel)
-  Quant div_n;                // magic/shift for dividing by N (only those fields used)
   int c16;                    // slab kernel: 16-bit counters, two copies per dword; strip kernel:
                               // 16-bit counters, two GLCMs per dword
   int kp;                     // strip kernel: GLCMs per partition (<= 4)
@@ -165,7 +163,7 @@ struct LaunchTiming {
 // Launchers (all asynchronous on `stream`; return the launch error).
 hipError_t launch_vote_generic(const VoteArgs& a, int dtype_bytes, int wg, size_t lds_bytes, hipStream_t stream,
                                const LaunchTiming& tm = {});
-hipError_t launch_vote_rows(const VoteArgs& a, int dtype_bytes, int maxdy, int rpw, int wg, size_t lds_bytes,
+hipError_t launch_vote_rows(const VoteArgs& a, int dtype_bytes, int maxdy, int wg, size_t lds_bytes,
                             hipStream_t stream, const LaunchTiming& tm = {});
 // D = dwords per bin (4, 8, 16 or 32), maxdy = 1, 2 or 4 (the ring holds maxdy + 1 rows).
 hipError_t launch_vote_strips(const VoteArgs& a, int dtype_bytes, int maxdy, int D, int wg, size_t lds_bytes,

@@ -100,7 +100,6 @@ struct OnehotArgs {
   uint32_t words_total;       // K N N
   uint32_t* xbuf;             // per-XCD slices, or null: one workgroup stores to out
   uint32_t* out;
-  int accumulate;             // (out only)
 };
 // Threads per workgroup and workgroups a CU holds (registers: 128 a lane, 168
 // at a reach of 4).

@@ -37,8 +37,7 @@ __global__ __launch_bounds__(onehot_threads(R), R == 4 ? 3 : 4) void k_vote_oneh
       if (a.xbuf) {
         if (c) __hip_atomic_fetch_add(xs + (uint32_t)k * NN + i * N + j, c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       } else {
-        uint32_t* o = a.out + (uint32_t)k * NN + i * N + j;
-        *o = (a.accumulate ? *o : 0u) + c;
+        a.out[(uint32_t)k * NN + i * N + j] = c;
       }
     }
   }

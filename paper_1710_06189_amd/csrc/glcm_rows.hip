@@ -31,8 +31,8 @@ namespace {
 // come, 5 more of bank conflicts, whatever the vector instructions next to it
 // (4.1 a vote; with 4.8 and 5.8 the 8192^2 image took the same time).  Measured
 // on MI355X (slabs of four rows read with their halo, before, and this walk):
-// 8192^2 u16 band, N = 64, 12 offsets 233 to 224 us; u8 crops, 7 offsets: 2937 x
-// 3015 noise, N = 16, 24.8 to 21.9, 1531 x 1489 smooth, N = 64, 30.5 to 29.7.
+// 8192^2 u16 band, N = 64, 12 offsets 236 to 224 us; u8 crops, 7 offsets: 2937 x
+// 3015 noise, N = 16, 24.8 to 21.9, 1531 x 1489 smooth, N = 64, 29.8 and 29.8.
 // Four rows at a time instead of two: 259, 23.0, 33.8 (registers).
 // ---------------------------------------------------------------------------
 struct Ring {
@@ -321,9 +321,8 @@ static hipError_t launch_rows_t(const VoteArgs& a, int maxdy, int wg, size_t lds
                      : launch_rows_u<Pix, false>(a, maxdy, wg, lds_bytes, stream, tm);
 }
 
-hipError_t launch_vote_rows(const VoteArgs& a, int dtype_bytes, int maxdy, int rpw, int wg, size_t lds_bytes,
+hipError_t launch_vote_rows(const VoteArgs& a, int dtype_bytes, int maxdy, int wg, size_t lds_bytes,
                             hipStream_t stream, const LaunchTiming& tm) {
-  if (rpw != 4) return hipErrorInvalidValue;
   return dtype_bytes == 1 ? launch_rows_t<uint8_t>(a, maxdy, wg, lds_bytes, stream, tm)
                           : launch_rows_t<uint16_t>(a, maxdy, wg, lds_bytes, stream, tm);
 }

@@ -25,7 +25,7 @@ struct StatsArgs {
   int vec;
 };
 constexpr int kHaralickStats = 13;
-constexpr int kHaralickMaxN = 1024;  // the marginal arrays (7 N doubles) fit the LDS
+constexpr int kHaralickMaxN = 1024;  // the marginals and distributions (5 N - 1 doubles) fit the LDS
 constexpr int kAverageMaxGroup = 64;
 
 hipError_t launch_symmetrize(const StatsArgs& a, hipStream_t stream);

@@ -321,7 +321,7 @@ __global__ __launch_bounds__(64 * W) void k_probability_wg(StatsArgs a) {
 // Natural logarithm of a positive normal double by table (Tang 1990): with x =
 // 2^e m, 1 <= m < 2, and c = 1 + k / 128 the point nearest to m,
 //     ln x = e ln 2 - ln(1/c) + ln(1 + r),  r = m (1/c) - 1,  |r| <= 2^-8,
-// the last by its series to r^6 (the next term is below 2^-58 |r|).  c = 1 has
+// the last by its series to r^6 (the next term is up to r^7 / 7, below 2^-50 |r|).  c = 1 has
 // 1/c = 1 and ln c = 0, and c = 2 has ln c = ln 2, so values next to 1 keep
 // their relative accuracy from both sides and ln 1 is 0.  17 instructions and
 // one LDS read, against about 60 of log().
