@@ -231,10 +231,10 @@ __global__ __launch_bounds__(WG) void k_batch(BatchArgs a) {
 // big item start on their own chunk, the others draw one from counter[1], and
 // each draws once more than it counts.  Who drew the last number sets the
 // counter back to zero.
-// Bound by the vector instructions that spread the masks (about 110 cycles a
-// wavefront and window row), then by the statistics.  Measured on MI355X, u8,
+// Bound by the vector instructions, which spread the masks (72 % of the SIMDs'
+// cycles; the products 34 %, at the same time).  Measured on MI355X, u8,
 // N = 16, d = 1 with the statistics: 4096 images of 32-512 px 214 us (counting
-// in LDS) to 112, 4096 of 64 x 64 51 us a pass, 1024 of 256 x 256 67.  Both
+// in LDS) to 113, 4096 of 64 x 64 51 us a pass, 1024 of 256 x 256 67.  Both
 // kinds of item go through one walk and one set of statistics: with a walk
 // each the code was 67 KB, more than the instruction cache, and a step took
 // 2.4 times as long (157 us).

@@ -107,12 +107,12 @@ __device__ __forceinline__ uint32_t varies(const uint32_t (&w)[D]) {
 // one entry in the workgroup's spill list each; there are at most (pairs of
 // the workgroup) / 2^15 of them.
 //
-// Bound: LDS atomics on random banks (one copy of the bins: the fullest of 32
-// banks serves three or four of 32 lanes, about 16 cycles per wavefront
-// instruction).  Measured on MI355X, 4096^2 u8 smooth, N = 256, 12 offsets (2.0e8
-// pairs): 112 us, 21 cycles a wavefront instruction with the looks at the bins
-// and the ends; 4 us more with an even row pitch.  The kernel before it, ten
-// ranges of the 12 GLCMs' bins over the whole image each, took 449 us.
+// Bound: the vector instructions of a vote (71 % of the SIMDs' cycles), then LDS
+// atomics on random banks (one copy of the bins; active 43 % of the time, two
+// thirds of it conflicts).  Measured on MI355X, 4096^2 u8 smooth, N = 256, 12
+// offsets (2.0e8 pairs): 111 us with the looks at the bins and the ends; 4 us more
+// with an even row pitch.  The kernel before it, ten ranges of the 12 GLCMs' bins
+// over the whole image each, took 449 us.
 template <typename Pix, bool BYTE, bool SLICED>
 __global__ __launch_bounds__(kLevelThreads) void k_vote_levels(LevelArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint32_t lds[];

@@ -41,9 +41,10 @@ constexpr double kMccTol = 1e-5;
 // a result tile, lane l holding rows r(g, v) of column i, is both operands of
 // the next squaring whatever r is, so no value ever moves between lanes.
 //
-// Bound: the fp64 matrix rate (a squaring at N = 16 is four instructions of 64
-// cycles, seven or so squarings a matrix) and the wavefront sum between two
-// squarings.  Measured on MI355X, 16384 matrices of N = 16: 36 us a call (57 us
+// Bound: vector instructions (650 a matrix, 59 % of the SIMDs' cycles), then the
+// products (22 of 64 cycles, 32 %), which overlap little with two wavefronts a SIMD
+// that each wait for a wavefront sum between two squarings.
+// Measured on MI355X, 16384 matrices of N = 16: 36 us a call (57 us
 // with one logarithm per squaring and a tolerance of 1e-10); cyclic Jacobi
 // rotations of S in LDS, the form before this one, took 2750 us (three
 // barriers for each of fifteen rounds of five or so sweeps).
