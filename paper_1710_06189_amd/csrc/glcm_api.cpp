@@ -410,10 +410,10 @@ bool blocks_fit(const glcm_plan_s* p) {
 // where its bins are 16-bit: several partitions of one copy each.  Measured on
 // MI355X, 4096^2 u8, per call against ranges of 16-bit bins that each walked
 // the whole image and merged through L2 atomics (smooth; noise; constant):
-// N = 256 with 12 offsets 120; 118; 307 us against 459; 1178; 875, with one
-// offset 38; 38; 107 against 82; 158; 131, N = 1024 with 2 offsets 76; 76; 169
+// N = 256 with 12 offsets 118; 117; 149 us against 459; 1178; 875, with one
+// offset 38; 38; 93 against 82; 158; 131, N = 1024 with 2 offsets 72; 73; 140
 // against 1064; 1132; 1133 (256 values counted), N = 128 with 12 offsets beyond
-// the row kernels' reach 113; 111; 266 against 297; 425; 863.
+// the row kernels' reach 112; 112; 108 against 297; 425; 863.
 bool levels_plan(const glcm_plan_s* p) {
   const glcm_tuning_t& t = p->tuning;
   return (t.path == kPathGeneric || t.path == kPathPartitioned) && t.counter_bits == 16 && t.partitions >= 2 &&

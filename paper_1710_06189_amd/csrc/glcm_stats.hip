@@ -450,7 +450,7 @@ __device__ __forceinline__ double group_sum(double v) {
 // square root, an exponential, divisions) runs for up to kPark matrices at
 // once, a lane each.
 // Bound: VALU issue (fp64).  Measured on MI355X, 16384 matrices of N = 16:
-// 22.4 us; 83.8 us when lane l walked row, column and diagonals one after the
+// 23.4 us; 83.8 us when lane l walked row, column and diagonals one after the
 // other, every statistic was summed bin by bin over the whole wavefront and
 // the logarithms were log()'s.
 constexpr int kPark = 4;
@@ -585,7 +585,7 @@ __global__ __launch_bounds__(kStatsThreads, L == 16 ? 4 : 3) void k_haralick_wav
 // consecutive words (32 bits wide where the total fits, else 64).  A quarter
 // of the wavefronts then reduces each distribution.
 // Bound: VALU issue and the LDS of the one CU that holds the matrix.
-// Measured on MI355X, 12 matrices of N = 256: 51 us (282 us with 256 threads,
+// Measured on MI355X, 12 matrices of N = 256: 55 us (282 us with 256 threads,
 // a thread per diagonal and three logarithm terms a bin).
 template <int W>
 __device__ __forceinline__ void haralick_bins(const uint32_t* P, int N, double T, double inv, uint32_t* ps, uint32_t* pd,
