@@ -894,6 +894,13 @@ hipError_t launch_haralick(const StatsArgs& a, hipStream_t stream) {
     else hipLaunchKernelGGL((k_haralick_wave<32, false>), grid, block, 0, stream, a);
     return hipGetLastError();
   }
+  // Workgroups of four wavefronts once the matrices outnumber the CUs (a second
+  // one waits for the first then, with sixteen), up to the N where the walk of a
+  // matrix by four is a good deal longer.  Measured on MI355X, us a call, four; sixteen wavefronts:
+  // K = 256 N = 33 11.6; 19.4, 64 16.3; 21.2, 96 27.1; 26.0, 128 34.7; 28.8.  K = 257
+  // N = 33 11.9; 30.4, 96 27.8; 44.5, 128 35.1; 49.2, 160 53.4; 66.4.  K = 1024 N = 64
+  // 21.0; 75.2, 96 44.4; 95.1, 128 57.2; 106, 160 90.3; 140; K = 512 N = 160 77.6; 71.3.
+  // So the line lies low in N above 256 matrices, and at N <= 64 below them.
   const size_t lds = (size_t)(5 * a.N - 1) * sizeof(double);
   if (a.N <= 96 && a.K > 256)
     hipLaunchKernelGGL(k_haralick<4>, dim3(grid_for((uint64_t)a.K, 8192)), dim3(256), (uint32_t)lds, stream, a);
